@@ -22,8 +22,12 @@
 #include <vector>
 
 #include "sno.h"
+#include "sno_fused.hpp"
 
 namespace {
+
+using snof::gelu_d;
+using snof::gelu_f;
 
 typedef short bf4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
@@ -364,18 +368,6 @@ void gemm(hipStream_t st, int batch, int M, int N, int K, int KB, const float* A
 }
 
 // ---------------------------------------------------------------------------
-constexpr float GELU_C = 0.7978845608028654f;   // sqrt(2 / pi)
-
-__device__ __forceinline__ float gelu_f(float x)
-{
-    return 0.5f * x * (1.f + tanhf(GELU_C * (x + 0.044715f * x * x * x)));
-}
-__device__ __forceinline__ float gelu_d(float x)
-{
-    const float th = tanhf(GELU_C * (x + 0.044715f * x * x * x));
-    return 0.5f * (1.f + th) + 0.5f * x * (1.f - th * th) * GELU_C * (1.f + 3.f * 0.044715f * x * x);
-}
-
 __global__ void k_gelu(const float* __restrict__ z, float* __restrict__ y, long n)
 {
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
@@ -404,6 +396,16 @@ __device__ __forceinline__ float four_feat(const Feat& f, int q, int sine, int t
     const float ph = f.cyc[q] * (float)t / (float)T;
     const float r = 2.f * 3.14159265358979f * (ph - floorf(ph));
     return sine ? sinf(r) : cosf(r);
+}
+
+// the sample-independent series of the lift inputs, [2 + 2 n_four][T]: ones,
+// t / T, the cos and sin features
+__global__ void k_lift_table(Feat f, int T, float* __restrict__ tab)
+{
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < (2 + 2 * f.n_four) * T; e += gridDim.x * blockDim.x) {
+        const int r = e / T, t = e - r * T;
+        tab[e] = r == 0 ? 1.f : r == 1 ? (float)t / (float)T : four_feat(f, (r - 2) >> 1, r & 1, t, T);
+    }
 }
 
 __global__ void k_features(const float* __restrict__ X, Feat f, int B, int T, int NA, float* __restrict__ A)
@@ -521,14 +523,25 @@ __device__ __forceinline__ double wave_min(double v)
     return v;
 }
 
-// bisection steps for the ray's horizontal slowness: to 2^-32 of the
-// smallest slowness, which moves the travel time by at most the horizontal
-// distance times that (6e-11 s over a kilometre where the fastest layer runs
-// at 4 km/s)
-constexpr int RAY_ITERS = 32;
-
 // One wave per (source b, frame f, receiver r); its lanes take the cell
 // layers of the path in turn and the sums over layers are wave reductions.
+//
+// Two-point ray (Snell's law across the cell layers): with the horizontal
+// slowness written p = s_min q / sqrt(1 + q^2), a layer of slowness s and
+// thickness t runs t s_min q / sqrt(s^2 + (s^2 - s_min^2) q^2) horizontally,
+// a concave, increasing function of q (linear in the fastest layers), so
+// Newton's steps from q = 0 approach the root from below, quadratically, and
+// stop when they no longer move it (5 to 8 steps; 40 bound the loop).  FP64
+// square roots and divisions are what the kernel spends its time on: bisection
+// by the same sums, 32 of them, took 30.4 us for 32 sources x 2 frames x 64
+// receivers; this takes 19 us for 64 sources.  The horizontal slowness is then
+// put on the grid that 32 halvings of [0, s_min] end on (2^-32 of s_min moves
+// the time by at most the horizontal distance times that: 6e-11 s over a
+// kilometre at 4 km/s), so that delays, and trainings that rest on them, do
+// not depend on how the root is found.
+constexpr int RAY_ITERS = 40;
+constexpr int RAY_GRID = 32;
+
 __global__ __launch_bounds__(256) void k_shifts(const float* __restrict__ X, Rays ry, int B, float* __restrict__ shift)
 {
     const int lane = threadIdx.x & 63;
@@ -554,19 +567,30 @@ __global__ __launch_bounds__(256) void k_shifts(const float* __restrict__ X, Ray
             const double L = sqrt(hor * hor + dz * dz);
             tau = k0 == k1 ? L * sl[ks] : L / fabs(dz) * fabs(ry.cum[f * ry.nz + ks] - ry.cum[f * ry.nz + kr]);
         } else {
-            // two-point ray (Snell's law across the cell layers): horizontal
-            // slowness p by bisection so that the layers' horizontal runs
-            // t p / sqrt(s^2 - p^2) add up to the horizontal distance; layer
-            // thickness half a cell at each end, a whole cell between
-            double lo = 0.0, hi = smin;
+            // layer thickness half a cell at each end, a whole cell between
+            double q = 0.0;
             for (int it = 0; it < RAY_ITERS; ++it) {
-                const double p = 0.5 * (lo + hi);
-                double run = 0.0;
+                // run / q and its derivative: t smin rho and t smin s^2 rho^3
+                double run = 0.0, der = 0.0;
                 for (int k = k0 + lane; k <= k1; k += 64) {
-                    const double t = (k == k0 || k == k1 ? 0.5 : 1.0) * ry.h[2];
-                    run += t * p / sqrt(sl[k] * sl[k] - p * p);
+                    const double t = (k == k0 || k == k1 ? 0.5 : 1.0) * ry.h[2] * smin, s2 = sl[k] * sl[k];
+                    const double rho = rsqrt(s2 + (s2 - smin * smin) * (q * q));
+                    run += t * rho;
+                    der += t * rho * (s2 * rho * rho);
                 }
-                if (wave_sum(run) < hor) lo = p;
+                run = wave_sum(run);
+                der = wave_sum(der);
+                const double step = (hor - run * q) / der;
+                q += step;
+                if (!(fabs(step) > 1e-13 * q)) break;   // the same in every lane
+            }
+            // p on the grid of RAY_GRID halvings of [0, s_min]: the cell of
+            // the root, its middle
+            const double root = smin * q / sqrt(1.0 + q * q);
+            double lo = 0.0, hi = smin;
+            for (int it = 0; it < RAY_GRID; ++it) {
+                const double p = 0.5 * (lo + hi);
+                if (p < root) lo = p;
                 else hi = p;
             }
             const double p = 0.5 * (lo + hi);
@@ -590,30 +614,58 @@ __device__ __forceinline__ void lagrange4(float w, float* c)
     c[3] = (w + 1.f) * w * (w - 1.f) * (1.f / 6.f);
 }
 
-// Y[b][o][t] = sum_f Yf[b][f O + o](t - shift[b][f][o mod n_rec])
-__global__ __launch_bounds__(256) void k_fcomb(const float* __restrict__ Yf, const float* __restrict__ shift, int B,
-                                               int F, int O, int n_rec, int T, float* __restrict__ Y)
+// Y[b][o][t] = scale[o / n_rec] sum_f Yf[b][f O + o](t - shift[b][f][o mod n_rec])
+// (scale null: 1).  A block takes one row (b, o): its F input rows go through
+// LDS (16-byte loads; four zeros at either end, so that positions outside the
+// window need no branch), and each thread forms four neighbouring samples.
+// Bound by memory: 12 bytes per output sample at two frames.
+template <int F>
+__global__ __launch_bounds__(256) void k_fcomb(const float* __restrict__ Yf, const float* __restrict__ shift, int rows,
+                                               int O, int n_rec, int T, const float* __restrict__ scale,
+                                               float* __restrict__ Y)
 {
-    // block rows (b, o), threads along t
-    const long per = (long)O * T;
-    for (int row = blockIdx.y; row < B * O; row += gridDim.y) {
+    extern __shared__ float fr_s[];   // F rows of T + 8
+    const int TP = T + 8;
+    for (int row = blockIdx.x; row < rows; row += gridDim.x) {
         const int b = row / O, o = row - b * O;
-        for (int t = blockIdx.x * 256 + threadIdx.x; t < T; t += gridDim.x * 256) {
-            float acc = 0.f;
-            for (int fr = 0; fr < F; ++fr) {
-                const float x = (float)t - shift[(b * F + fr) * n_rec + o % n_rec];
-                const float fl = floorf(x);
-                float c[4];
-                lagrange4(x - fl, c);
-                const int i0 = (int)fl - 1;
-                const float* u = Yf + ((long)b * F + fr) * per + (long)o * T;
+        __syncthreads();
+        if (threadIdx.x < F * 8) fr_s[(threadIdx.x >> 3) * TP + ((threadIdx.x & 7) < 4 ? 0 : T) + (threadIdx.x & 7)] = 0.f;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int i = i0 + k;
-                    if (i >= 0 && i < T) acc += c[k] * u[i];
-                }
+        for (int f = 0; f < F; ++f) {
+            const float* __restrict__ u = Yf + (((long)b * F + f) * O + o) * T;
+            for (int t = threadIdx.x * 4; t < T; t += 1024) {
+                const float4 v = *reinterpret_cast<const float4*>(u + t);
+                float* d = fr_s + f * TP + 4 + t;
+                d[0] = v.x;
+                d[1] = v.y;
+                d[2] = v.z;
+                d[3] = v.w;
             }
-            Y[(long)row * T + t] = acc;
+        }
+        __syncthreads();
+        const float sc = scale ? scale[o / n_rec] : 1.f;
+        float sh[F];
+#pragma unroll
+        for (int f = 0; f < F; ++f) sh[f] = shift[(b * F + f) * n_rec + o % n_rec];
+        for (int t = threadIdx.x * 4; t < T; t += 1024) {
+            float acc[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc[i] = 0.f;
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    const float x = (float)(t + i) - sh[f];
+                    const float fl = floorf(x);
+                    float c[4];
+                    lagrange4(x - fl, c);
+                    // first tap fl - 1, moved into the zeros where all four are outside
+                    const float* u = fr_s + f * TP + 4 + (int)fminf(fmaxf(fl - 1.f, -4.f), (float)T);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) acc[i] += c[k] * u[k];
+                }
+                if (scale) acc[i] *= sc;
+            }
+            *reinterpret_cast<float4*>(Y + (long)row * T + t) = make_float4(acc[0], acc[1], acc[2], acc[3]);
         }
     }
 }
@@ -982,6 +1034,28 @@ __global__ void k_head(const float* __restrict__ phi, const float* __restrict__ 
     est[b] = expf(fminf(s, 30.f));
 }
 
+// the same from per-tile sums of the last hidden layer, pool[b][tile][c] (tiles
+// of 64 samples): one wave per sample
+__global__ __launch_bounds__(64) void k_head_tiles(const float* __restrict__ pool, const float* __restrict__ X, Feat f,
+                                                   const float* __restrict__ h, int C, int T, float margin,
+                                                   float* __restrict__ est)
+{
+    const int b = blockIdx.x, lane = threadIdx.x, nt = T / 64;
+    float s = 0.f;
+    if (lane < C) {
+        float m = 0.f;
+        for (int i = 0; i < nt; ++i) m += pool[((long)b * nt + i) * C + lane];
+        s = h[lane] * (m / T);
+    }
+    for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
+    if (lane == 0) {
+        s += margin;
+        for (int j = 0; j < 6; ++j) s += h[C + j] * mfeat(X, f, b, j);
+        s += h[C + 6];
+        est[b] = expf(fminf(s, 30.f));
+    }
+}
+
 __global__ void k_decim(const float* __restrict__ in, long rows, int nt, int decim, float* __restrict__ out)
 {
     const int no = nt / decim;
@@ -1011,6 +1085,10 @@ struct sno {
     long off_P, off_pb, off_W[16], off_b[16], off_Rr[16], off_Ri[16], off_Q1, off_q1b, off_Q2, off_q2b;
     float *theta = nullptr, *grad = nullptr, *m1 = nullptr, *m2 = nullptr;
     float *Fb = nullptr, *G = nullptr;   // truncated DFT bases
+    float *Ft = nullptr, *Gt = nullptr;  // their transposes, [2K][T] and [T][2K]
+    float* lift_tab = nullptr;           // series of the lift inputs (k_lift_table)
+    int* lift_meta = nullptr;            // per lift channel its series and factor (snof::LiftP)
+    bool fused = false;                  // the fused kernels' range (fused_ok)
     float *dscale = nullptr;
     float scale[4] = {1, 1, 1, 1};
     std::vector<float> head;
@@ -1030,6 +1108,11 @@ struct sno {
           *part = nullptr, *lossd = nullptr, *phi = nullptr, *Xb = nullptr, *Yb = nullptr, *Y6 = nullptr,
           *dY6 = nullptr, *shift = nullptr, *Qm = nullptr, *dQm = nullptr, *bm = nullptr, *dbm = nullptr;
     int* idxd = nullptr;
+    // inference workspace of the fused path: trunk chunks of up to ibt
+    // samples, projection chunks of up to ibh
+    int ibt = 0, ibh = 0;
+    float *iV[2] = {nullptr, nullptr}, *iVh = nullptr, *iUh = nullptr, *ipool = nullptr, *iQm = nullptr, *ibm = nullptr,
+          *iY = nullptr, *ishift = nullptr;
     // partial sums of the split weight-gradient products
     static constexpr long kws_n = 4L << 20;
     float* kws = nullptr;
@@ -1050,10 +1133,20 @@ struct sno {
         idxd = nullptr;
         bmax = 0;
     }
+    void free_iws()
+    {
+        for (float** p : {&iV[0], &iV[1], &iVh, &iUh, &ipool, &iQm, &ibm, &iY, &ishift}) {
+            (void)hipFree(*p);
+            *p = nullptr;
+        }
+        ibt = ibh = 0;
+    }
     ~sno()
     {
         free_ws();
-        for (float* p : {theta, grad, m1, m2, Fb, G, dscale, dhead}) (void)hipFree(p);
+        free_iws();
+        for (float* p : {theta, grad, m1, m2, Fb, G, Ft, Gt, lift_tab, dscale, dhead}) (void)hipFree(p);
+        (void)hipFree(lift_meta);
         (void)hipFree(drec);
         (void)hipFree(dcum);
         (void)hipFree(dslow);
@@ -1076,6 +1169,26 @@ struct sno {
             hipMalloc(&idxd, B * sizeof(int)))
             return sfail(PSTD_ENOMEM, "surrogate workspace");
         bmax = B;
+        return PSTD_OK;
+    }
+
+    // workspace of an inference over n samples (grown, never shrunk)
+    static constexpr int IBT = 256, IBH = 64;
+    int ensure_infer(int n)
+    {
+        const int bt = std::min(n, IBT), bh = std::min(n, IBH);
+        if (bt <= ibt && bh <= ibh) return PSTD_OK;
+        free_iws();
+        const long C = cfg.C, T = cfg.T, K2 = 2 * cfg.K, FO = (long)F * O;
+        auto al = [&](float** p, long m) { return hipMalloc(p, std::max<long>(m, 1) * sizeof(float)); };
+        if (al(&iV[0], bt * C * T) || al(&iV[1], bt * C * T) || al(&iVh, bt * C * K2) || al(&iUh, bt * C * K2) ||
+            al(&ipool, bt * (T / 64) * C) || al(&iQm, bh * ((FO + 15) / 16 * 16) * cfg.H) || al(&ibm, bh * FO) || al(&iY, bh * FO * T) ||
+            al(&ishift, (long)bh * F * cfg.n_rec)) {
+            free_iws();
+            return sfail(PSTD_ENOMEM, "surrogate inference workspace");
+        }
+        ibt = bt;
+        ibh = bh;
         return PSTD_OK;
     }
 };
@@ -1148,6 +1261,128 @@ bool cfg_ok(const sno_cfg* c)
     return true;
 }
 
+// The fused kernels' range: the widths they are built for, up to 16 modes,
+// whole 128-sample tiles of time and 32-deep slices of hidden rows, float4
+// operands.  Everything else goes through the general GEMM.
+bool fused_ok(const sno* s)
+{
+    const sno_cfg& c = s->cfg;
+    return (c.C == 32 || c.C == 64) && c.K >= 8 && c.K <= 16 && c.K % 2 == 0 && c.T % 128 == 0 && s->NA >= 16 &&
+           s->NA % 4 == 0 && c.H % 32 == 0 && s->F * s->O >= 32;
+}
+
+// Lift and Fourier layers of B samples through the fused kernels: V[l] the
+// input of layer l (V[L] the last layer's output), Z[l] the pre-activations
+// (may be null), Vh[l] the spectra; A and pool may be null
+template <int C>
+void trunk_c(sno* s, hipStream_t st, const float* X, int B, int TS, float* A, float* const* V, float* const* Z,
+             float* const* Vh, float* Uh, float* pool)
+{
+    const sno_cfg& c = s->cfg;
+    const int T = c.T, K2 = 2 * c.K;
+    const float* th = s->theta;
+    snof::LiftP lp{X, th + s->off_P, th + s->off_pb, s->lift_tab, s->lift_meta, {}, {}, s->NA, 2 + 2 * c.n_four, T, TS,
+                   A, V[0]};
+    for (int i = 0; i < 3; ++i) {
+        lp.off[i] = s->feat.off[i];
+        lp.inv[i] = s->feat.inv[i];
+    }
+    const dim3 tiles(T / 64, B);
+    hipLaunchKernelGGL((snof::k_lift<C>), tiles, dim3(256), (size_t)lp.rows * 64 * sizeof(float), st, lp);
+    for (int l = 0; l < c.L; ++l) {
+        if (K2 >= 32) snof::launch_dft<32, false>(st, B, V[l], nullptr, nullptr, s->Ft, C, T, TS, K2, Vh[l]);
+        else snof::launch_dft<16, false>(st, B, V[l], nullptr, nullptr, s->Ft, C, T, TS, K2, Vh[l]);
+        hipLaunchKernelGGL((snof::k_cmix_f<C>), dim3(c.K, (B + snof::MB - 1) / snof::MB, C / 32), dim3(256), 0, st,
+                           th + s->off_Rr[l], th + s->off_Ri[l], Vh[l], B, c.K, Uh);
+        const bool last = l == c.L - 1;
+        const snof::ZP zp{th + s->off_W[l], th + s->off_b[l], V[l], Uh, s->Gt, T, TS, K2,
+                          last ? V[l + 1] : Z ? Z[l] : nullptr, last ? nullptr : V[l + 1], last ? pool : nullptr};
+        hipLaunchKernelGGL((snof::k_zlayer<C, false>), tiles, dim3(256), 0, st, zp);
+    }
+}
+
+void trunk(sno* s, hipStream_t st, const float* X, int B, int TS, float* A, float* const* V, float* const* Z,
+           float* const* Vh, float* Uh, float* pool)
+{
+    if (s->cfg.C == 64) trunk_c<64>(s, st, X, B, TS, A, V, Z, Vh, Uh, pool);
+    else trunk_c<32>(s, st, X, B, TS, A, V, Z, Vh, Uh, pool);
+}
+
+// Tiles of the fused projection, largest first: NW RW 16 outputs x NTC 16 time
+// samples per block
+template <int RW, int NTC, int NW>
+bool try_proj(sno* s, hipStream_t st, snof::ProjP p, int B, bool last)
+{
+    constexpr int M = RW * NW * 16, N = NTC * 16;
+    p.nt = p.T / N;
+    p.nm = (p.FO + M - 1) / M;
+    p.B = B;
+    if (!last && (M >= 2 * p.FO || (long)B * p.nt * p.nm < 256)) return false;
+    const int slots = B < snof::XCD_COUNT ? B : (B + snof::XCD_COUNT - 1) / snof::XCD_COUNT * snof::XCD_COUNT;
+    const dim3 grid((unsigned)(slots * p.nt * p.nm));
+    if (s->cfg.C == 64) hipLaunchKernelGGL((snof::k_proj<64, RW, NTC, NW>), grid, dim3(NW * 64), 0, st, p);
+    else hipLaunchKernelGGL((snof::k_proj<32, RW, NTC, NW>), grid, dim3(NW * 64), 0, st, p);
+    return true;
+}
+
+// The largest tile that gives each of the 256 compute units a block and does
+// not leave half its rows empty.  A block's hidden values are formed anew in
+// every tile of output rows, so the tall tiles do the least work; the small
+// ones are there for latency.  Prediction of 1, 4, 16 and 64 sources at 1024
+// hidden and 2 x 256 output series, whole call: 512 x 128 tiles 192, 198, 228,
+// 416 us; 256 x 32: 163, 170, 244, 612; 64 x 32: 153, 187, 340, 942.
+void proj(sno* s, hipStream_t st, const snof::ProjP& p, int B)
+{
+    try_proj<4, 8, 8>(s, st, p, B, false) || try_proj<4, 4, 8>(s, st, p, B, false) ||
+        try_proj<2, 8, 8>(s, st, p, B, false) || try_proj<2, 4, 8>(s, st, p, B, false) ||
+        try_proj<1, 8, 8>(s, st, p, B, false) || try_proj<2, 2, 8>(s, st, p, B, false) ||
+        try_proj<1, 2, 8>(s, st, p, B, false) || try_proj<1, 2, 4>(s, st, p, B, true);
+}
+
+// Outputs of n samples through the fused kernels (fused_ok): Y (16-byte
+// aligned) [n][4][n_rec][T], times scale per component if not null; est (may
+// be null) the error head's estimates.  The trunk runs in chunks of IBT
+// samples, the projection in chunks of IBH, whose weighted projections and
+// frames (4 MB per sample at 1024 hidden and 2 x 256 output series) then stay
+// in the last-level cache between the kernels that write and read them.
+int infer(sno* s, hipStream_t st, const float* X, int n, float* Y, const float* scale, float* est)
+{
+    const sno_cfg& c = s->cfg;
+    int rc = s->ensure_infer(n);
+    if (rc) return rc;
+    const int T = c.T, TS = T, H = c.H, O = s->O, FO = s->F * O;
+    const float* th = s->theta;
+    for (int b0 = 0; b0 < n; b0 += s->ibt) {
+        const int B = std::min(s->ibt, n - b0);
+        const float* Xb = X + (long)b0 * 9;
+        float *V[17], *Vh[16];
+        for (int l = 0; l <= c.L; ++l) V[l] = s->iV[l & 1];
+        for (int l = 0; l < c.L; ++l) Vh[l] = s->iVh;
+        trunk(s, st, Xb, B, TS, nullptr, V, nullptr, Vh, s->iUh, est ? s->ipool : nullptr);
+        if (est)
+            hipLaunchKernelGGL(k_head_tiles, dim3(B), dim3(64), 0, st, s->ipool, Xb, s->feat, s->dhead, c.C, T,
+                               s->head_margin, est + b0);
+        for (int h0 = 0; h0 < B; h0 += s->ibh) {
+            const int Bh = std::min(s->ibh, B - h0);
+            const float* Xh = Xb + (long)h0 * 9;
+            float* Yh = Y + (long)(b0 + h0) * O * T;
+            snof::MixP mp{th + s->off_Q2, th + s->off_q2b, Xh, {}, Bh, FO, O, H, s->iQm, s->ibm};
+            for (int j = 0; j < 6; ++j) mp.inv[j] = s->feat.inv[3 + j];
+            hipLaunchKernelGGL(snof::k_qmix_frag, dim3(H / 32, (FO + 15) / 16), dim3(128), 0, st, mp);
+            snof::ProjP pp{V[c.L] + (long)h0 * c.C * TS, th + s->off_Q1, th + s->off_q1b, s->iQm, s->ibm,
+                           s->F == 1 ? scale : nullptr, T, TS, H, FO, c.n_rec, 0, 0, 0, s->F == 1 ? Yh : s->iY};
+            proj(s, st, pp, Bh);
+            if (s->F == 2) {
+                hipLaunchKernelGGL(k_shifts, dim3((unsigned)std::min<long>(((long)Bh * 2 * c.n_rec + 3) / 4, 8192)),
+                                   dim3(256), 0, st, Xh, s->rays, Bh, s->ishift);
+                hipLaunchKernelGGL(k_fcomb<2>, dim3((unsigned)std::min<long>((long)Bh * O, 65535)), dim3(256),
+                                   2 * (T + 8) * sizeof(float), st, s->iY, s->ishift, Bh * O, O, c.n_rec, T, scale, Yh);
+            }
+        }
+    }
+    return PSTD_OK;
+}
+
 // forward of B samples whose raw features are X (device); leaves the caches in s
 void forward(sno* s, hipStream_t st, const float* X, int B)
 {
@@ -1155,33 +1390,43 @@ void forward(sno* s, hipStream_t st, const float* X, int B)
     const long C = c.C, T = c.T, K = c.K, K2 = 2 * K, H = c.H, O = s->O;
     const float* th = s->theta;
     const long NA = s->NA;
-    hipLaunchKernelGGL(k_features, dim3(grid_for(B * NA * T)), dim3(256), 0, st, X, s->feat, B, (int)T, (int)NA, s->A);
-    gemm(st, B, C, T, NA, 1, th + s->off_P, NA, 1, 0, 0, s->A, T, 1, NA * T, 0, s->V(0), T, 1, C * T, 1.f, 0.f,
-         th + s->off_pb);
-    for (int l = 0; l < c.L; ++l) {
-        float* V = s->V(l);
-        float* Vh = s->Vhl(l);
-        float* Z = s->Zl(l);
-        // truncated DFT along time
-        gemm(st, B, C, K2, T, 1, V, T, 1, C * T, 0, s->Fb, K2, 1, 0, 0, Vh, K2, 1, C * K2);
-        // complex mixing per mode: batch over modes, samples as columns
-        const float* Rr = th + s->off_Rr[l];
-        const float* Ri = th + s->off_Ri[l];
-        if (mix_lds(C) <= MIX_LDS_MAX) {
-            hipLaunchKernelGGL(k_cmix<false>, dim3((unsigned)K), dim3(256), mix_lds(C), st, Rr, Ri, Vh, B, (int)C,
-                               (int)K, s->Uh);
-        } else {
-            gemm(st, K, C, B, C, 1, Rr, C, 1, C * C, 0, Vh, K2, C * K2, 1, 0, s->Uh, K2, C * K2, 1, 1.f, 0.f);
-            gemm(st, K, C, B, C, 1, Ri, C, 1, C * C, 0, Vh + K, K2, C * K2, 1, 0, s->Uh, K2, C * K2, 1, -1.f, 1.f);
-            gemm(st, K, C, B, C, 1, Ri, C, 1, C * C, 0, Vh, K2, C * K2, 1, 0, s->Uh + K, K2, C * K2, 1, 1.f, 0.f);
-            gemm(st, K, C, B, C, 1, Rr, C, 1, C * C, 0, Vh + K, K2, C * K2, 1, 0, s->Uh + K, K2, C * K2, 1, 1.f, 1.f);
+    if (s->fused) {
+        float *V[17], *Vh[16], *Z[16];
+        for (int l = 0; l <= c.L; ++l) V[l] = s->V(l);
+        for (int l = 0; l < c.L; ++l) {
+            Vh[l] = s->Vhl(l);
+            Z[l] = s->Zl(l);
         }
-        // Z = W V + b + inverse DFT of the mixed modes
-        gemm(st, B, C, T, C, 1, th + s->off_W[l], C, 1, 0, 0, V, T, 1, C * T, 0, Z, T, 1, C * T, 1.f, 0.f,
-             th + s->off_b[l]);
-        gemm(st, B, C, T, K2, 1, s->Uh, K2, 1, C * K2, 0, s->G, T, 1, 0, 0, Z, T, 1, C * T, 1.f, 1.f);
-        if (l < c.L - 1)
-            hipLaunchKernelGGL(k_gelu, dim3(grid_for(B * C * T)), dim3(256), 0, st, Z, s->V(l + 1), (long)B * C * T);
+        trunk(s, st, X, B, (int)T, s->A, V, Z, Vh, s->Uh, nullptr);
+    } else {
+        hipLaunchKernelGGL(k_features, dim3(grid_for(B * NA * T)), dim3(256), 0, st, X, s->feat, B, (int)T, (int)NA, s->A);
+        gemm(st, B, C, T, NA, 1, th + s->off_P, NA, 1, 0, 0, s->A, T, 1, NA * T, 0, s->V(0), T, 1, C * T, 1.f, 0.f,
+             th + s->off_pb);
+        for (int l = 0; l < c.L; ++l) {
+            float* V = s->V(l);
+            float* Vh = s->Vhl(l);
+            float* Z = s->Zl(l);
+            // truncated DFT along time
+            gemm(st, B, C, K2, T, 1, V, T, 1, C * T, 0, s->Fb, K2, 1, 0, 0, Vh, K2, 1, C * K2);
+            // complex mixing per mode: batch over modes, samples as columns
+            const float* Rr = th + s->off_Rr[l];
+            const float* Ri = th + s->off_Ri[l];
+            if (mix_lds(C) <= MIX_LDS_MAX) {
+                hipLaunchKernelGGL(k_cmix<false>, dim3((unsigned)K), dim3(256), mix_lds(C), st, Rr, Ri, Vh, B, (int)C,
+                                   (int)K, s->Uh);
+            } else {
+                gemm(st, K, C, B, C, 1, Rr, C, 1, C * C, 0, Vh, K2, C * K2, 1, 0, s->Uh, K2, C * K2, 1, 1.f, 0.f);
+                gemm(st, K, C, B, C, 1, Ri, C, 1, C * C, 0, Vh + K, K2, C * K2, 1, 0, s->Uh, K2, C * K2, 1, -1.f, 1.f);
+                gemm(st, K, C, B, C, 1, Ri, C, 1, C * C, 0, Vh, K2, C * K2, 1, 0, s->Uh + K, K2, C * K2, 1, 1.f, 0.f);
+                gemm(st, K, C, B, C, 1, Rr, C, 1, C * C, 0, Vh + K, K2, C * K2, 1, 0, s->Uh + K, K2, C * K2, 1, 1.f, 1.f);
+            }
+            // Z = W V + b + inverse DFT of the mixed modes
+            gemm(st, B, C, T, C, 1, th + s->off_W[l], C, 1, 0, 0, V, T, 1, C * T, 0, Z, T, 1, C * T, 1.f, 0.f,
+                 th + s->off_b[l]);
+            gemm(st, B, C, T, K2, 1, s->Uh, K2, 1, C * K2, 0, s->G, T, 1, 0, 0, Z, T, 1, C * T, 1.f, 1.f);
+            if (l < c.L - 1)
+                hipLaunchKernelGGL(k_gelu, dim3(grid_for(B * C * T)), dim3(256), 0, st, Z, s->V(l + 1), (long)B * C * T);
+        }
     }
     gemm(st, B, H, T, C, 1, th + s->off_Q1, C, 1, 0, 0, s->V(c.L), T, 1, C * T, 0, s->Hp, T, 1, H * T, 1.f, 0.f,
          th + s->off_q1b);
@@ -1197,8 +1442,9 @@ void forward(sno* s, hipStream_t st, const float* X, int B)
         hipLaunchKernelGGL(k_shifts, dim3((unsigned)std::min<long>(((long)B * s->F * c.n_rec + 3) / 4, 4096)),
                            dim3(256), 0, st, X, s->rays, B,
                            s->shift);
-        hipLaunchKernelGGL(k_fcomb, rows_grid(T, B * O), dim3(256), 0, st, s->Y6, s->shift, B, s->F, (int)O, c.n_rec,
-                           (int)T, s->Y);
+        hipLaunchKernelGGL(k_fcomb<2>, dim3((unsigned)std::min<long>(B * O, 65535)), dim3(256),
+                           2 * (T + 8) * sizeof(float), st, s->Y6, s->shift, (int)(B * O), (int)O, c.n_rec, (int)T,
+                           nullptr, s->Y);
     }
 }
 
@@ -1325,7 +1571,7 @@ int sno_create(const sno_cfg* cfg, const float* params, sno** out)
     const long np = s->np;
     const int T = cfg->T, K = cfg->K;
     // DFT bases (double, rounded once): F (T x 2K) = [cos | -sin], G (2K x T)
-    std::vector<float> F((size_t)T * 2 * K), G((size_t)2 * K * T);
+    std::vector<float> F((size_t)T * 2 * K), G((size_t)2 * K * T), Ft(F.size()), Gt(G.size());
     for (int j = 0; j < T; ++j)
         for (int k = 0; k < K; ++k) {
             const double a = 2.0 * M_PI * (double)j * k / T;
@@ -1335,10 +1581,24 @@ int sno_create(const sno_cfg* cfg, const float* params, sno** out)
             G[(size_t)k * T + j] = (float)(w * std::cos(a) / T);
             G[(size_t)(K + k) * T + j] = (float)(-w * std::sin(a) / T);
         }
+    for (int j = 0; j < T; ++j)
+        for (int q = 0; q < 2 * K; ++q) {
+            Ft[(size_t)q * T + j] = F[(size_t)j * 2 * K + q];
+            Gt[(size_t)j * 2 * K + q] = G[(size_t)q * T + j];
+        }
+    s->fused = fused_ok(s);
+    // lift channels: series (row of lift_tab) | factor << 16
+    std::vector<int> meta((s->NA + 31) / 32 * 32, 4 << 16);
+    for (int k = 0; k < s->NA; ++k) {
+        const int j = k - 4 - 2 * cfg->n_four;   // position products: (frequency, position, cos / sin)
+        meta[k] = k < 3 ? k << 16 : k == 3 ? (1 | 3 << 16) : j < 0 ? ((k - 2) | 3 << 16)
+                                                           : ((2 + 2 * (j / 6) + (j & 1)) | ((j % 6) >> 1) << 16);
+    }
     int rc = PSTD_OK;
     if (hipMalloc(&s->theta, np * 4) || hipMalloc(&s->grad, np * 4) || hipMalloc(&s->m1, np * 4) ||
         hipMalloc(&s->m2, np * 4) || hipMalloc(&s->Fb, F.size() * 4) || hipMalloc(&s->G, G.size() * 4) ||
-        hipMalloc(&s->dscale, 16) || hipMalloc(&s->dhead, (cfg->C + 7) * 4))
+        hipMalloc(&s->Ft, Ft.size() * 4) || hipMalloc(&s->Gt, Gt.size() * 4) ||
+        hipMalloc(&s->lift_tab, (2 + 2 * cfg->n_four) * (size_t)T * 4) || hipMalloc(&s->lift_meta, meta.size() * 4) || hipMalloc(&s->dscale, 16) || hipMalloc(&s->dhead, (cfg->C + 7) * 4))
         rc = sfail(PSTD_ENOMEM, "surrogate parameters");
     if (!rc && cfg->frames == 2) {
         // ray tables: receivers, per-frame slowness and its depth integral to
@@ -1366,9 +1626,19 @@ int sno_create(const sno_cfg* cfg, const float* params, sno** out)
     if (!rc && (hipMemcpy(s->theta, params, np * 4, hipMemcpyHostToDevice) ||
                 hipMemcpy(s->Fb, F.data(), F.size() * 4, hipMemcpyHostToDevice) ||
                 hipMemcpy(s->G, G.data(), G.size() * 4, hipMemcpyHostToDevice) ||
+                hipMemcpy(s->Ft, Ft.data(), Ft.size() * 4, hipMemcpyHostToDevice) ||
+                hipMemcpy(s->Gt, Gt.data(), Gt.size() * 4, hipMemcpyHostToDevice) ||
                 hipMemcpy(s->dscale, s->scale, 16, hipMemcpyHostToDevice) || hipMemset(s->m1, 0, np * 4) ||
                 hipMemset(s->m2, 0, np * 4) || hipMemset(s->grad, 0, np * 4)))
         rc = sfail(PSTD_EDEVICE, "surrogate upload");
+    if (!rc && hipMemcpy(s->lift_meta, meta.data(), meta.size() * 4, hipMemcpyHostToDevice))
+        rc = sfail(PSTD_EDEVICE, "surrogate upload");
+    if (!rc) {
+        hipLaunchKernelGGL(k_lift_table, dim3(grid_for((2L + 2 * cfg->n_four) * T)), dim3(256), 0, nullptr, s->feat, T,
+                           s->lift_tab);
+        if (hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess)
+            rc = sfail(PSTD_EDEVICE, "surrogate time features");
+    }
     // error head defaults to "always unsure" until trained: exp(30)
     s->head.assign(cfg->C + 7, 0.f);
     s->head[cfg->C + 6] = 30.f;
@@ -1431,6 +1701,13 @@ int sno_forward(sno* s, const float* X, int n, float* Y, void* hip_stream)
 {
     if (!s || !X || !Y || n < 1) return sfail(PSTD_EINVAL, "bad arguments");
     hipStream_t st = (hipStream_t)hip_stream;
+    if (s->fused && (uintptr_t)Y % 16 == 0) {
+        int rc = infer(s, st, X, n, Y, nullptr, nullptr);
+        if (rc) return rc;
+        S_TRY(hipGetLastError());
+        S_TRY(hipStreamSynchronize(st));
+        return PSTD_OK;
+    }
     const int bs = 32;
     int rc = s->ensure(std::min(n, bs));
     if (rc) return rc;
@@ -1626,6 +1903,14 @@ int sno_predict(sno* s, const float* X, int n, float* Y, float* est_err, void* h
     if (!s || !X || !Y || n < 0) return sfail(PSTD_EINVAL, "bad arguments");
     hipStream_t st = (hipStream_t)hip_stream;
     const sno_cfg& c = s->cfg;
+    if (s->fused && (uintptr_t)Y % 16 == 0) {
+        if (n > 0) {
+            int rc = infer(s, st, X, n, Y, s->dscale, est_err);
+            if (rc) return rc;
+        }
+        S_TRY(hipGetLastError());
+        return PSTD_OK;
+    }
     const int bs = 32;
     int rc = s->ensure(bs);
     if (rc) return rc;

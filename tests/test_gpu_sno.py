@@ -430,3 +430,41 @@ def test_adam_steps_match_oracle(B):
         assert np.abs(gv - v).max() <= 1e-6 * np.abs(v).max(), step
         # each weight moves by about lr per step: compare the moves, relative to lr
         assert np.abs((gth - theta) - (th - theta)).max() <= 1e-4 * lr, step
+
+
+# ---------------------------------------------------------------------------
+# the fused inference kernels: edges of their tiles and of their range
+FUSED = [osno.Dims(four=(3.0, 7.0, 9.0, 12.5, 14.0, 15.0), C=32, T=128, K=8, L=1, H=32, O=36),
+         osno.Dims(four=(3.0, 7.0, 12.5), pos_mod=True, C=64, T=128, K=16, L=3, H=96, O=40),
+         osno.Dims(four=inputs.sno_fourier_cycles(16, 2.0, 40.0), pos_mod=True, C=64, T=512, K=10, L=2, H=160, O=520),
+         osno.Dims(four=inputs.sno_fourier_cycles(64, 1.0, 60.0), pos_mod=True, C=32, T=256, K=14, L=2, H=64, O=136)]
+
+
+@pytest.mark.parametrize("d", FUSED, ids=["c32_t128_k8", "c64_t128_k16", "c64_t512_o520", "c32_64_frequencies"])
+def test_fused_inference_matches_oracle_and_general_projection(B, d):
+    """Widths, mode counts, times and output counts at the edges of the fused
+    kernels' tiles, one sample and a chunk boundary (65 samples): against the
+    oracle (the BF16 bar of this file), and against the general projection,
+    which a prediction into a buffer that is not 16-byte aligned takes (the same
+    BF16 operands and FP32 sums: 1e-6)."""
+    import ctypes
+    import torch
+    rng = np.random.default_rng(40)
+    theta = (init(d, 41) + 0.02 * rng.standard_normal(osno.n_params(d))).astype(np.float32).astype(np.float64)
+    s = make(B, d, theta)
+    X = rng.uniform(-1, 1, (65, 9))
+    Xd = torch.tensor(X, dtype=torch.float32, device="cuda")
+    Y, est = s.predict(Xd)
+    assert np.isfinite(est.cpu().numpy()).all()
+    few = [0, 31, 63, 64]
+    ref = osno.forward(theta, X[few], d)
+    got = Y.cpu().numpy().reshape(65, d.O, d.T)
+    assert rel(got[few], ref) < 2e-2
+    one, _ = s.predict(Xd[64:])
+    assert rel(one.cpu().numpy().reshape(1, d.O, d.T), got[64:].astype(np.float64)) <= 1e-6
+    flat = torch.zeros(65 * d.O * d.T + 4, dtype=torch.float32, device="cuda")
+    rc = B._L.sno_predict(s._h, B._dev(Xd), 65, ctypes.c_void_p(flat.data_ptr() + 4), None, B._stream_handle())
+    assert rc == 0
+    gen = flat[1:1 + Y.numel()].cpu().numpy().reshape(65, d.O, d.T)
+    assert rel(got, gen.astype(np.float64)) <= 1e-6
+    assert float(flat[0]) == 0.0 and (flat[1 + Y.numel():] == 0.0).all()
