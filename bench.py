@@ -31,7 +31,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 METRIC = "Gcell-steps/s FP32 PSTD elastic @1e-4 L2; surrogate vs solver seismograms/s"
 KERNEL_SOURCES = ["paper_1705_04874_amd/csrc/pstd_kernels.hpp", "paper_1705_04874_amd/csrc/fft_lds.hpp",
-                  "paper_1705_04874_amd/csrc/pstd3d.hip"]
+                  "paper_1705_04874_amd/csrc/pstd3d.hip", "paper_1705_04874_amd/csrc/pstd_variants.hip",
+                  "paper_1705_04874_amd/csrc/pstd_variants.hpp"]
 
 # HBM bytes per launch measured with rocprofv3 (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, the
 # factors a 1 GiB device copy gives) on kernel sources whose digest is recorded here; the

@@ -8,7 +8,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpstd3d.so")
-SOURCES = ["pstd3d.hip", "combine.hip", "sno.hip", "catalog.hip"]
+# (source, object, extra flags): the solver's kernels are compiled per group of
+# grid lengths, side by side (pstd_variants.hpp)
+SOURCES = [("pstd_variants.hip", f"pstd_variants_{g}.o", [f"-DPSTD_GROUP={g}"]) for g in range(8)]
+SOURCES += [(s, s + ".o", []) for s in ("sno.hip", "combine.hip", "pstd3d.hip", "catalog.hip")]
 
 # Packed FP32 instructions are disabled for every HIP translation unit.
 HIPFLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -20,10 +23,10 @@ def build(verbose=True, jobs=None):
     objs = []
     t0 = time.time()
     procs = []
-    for s in SOURCES:
+    for s, o, flags in SOURCES:
         src = os.path.join(CSRC, s)
-        obj = os.path.join(CSRC, s + ".o")
-        cmd = ["hipcc", "-c"] + HIPFLAGS + ["-o", obj, src]
+        obj = os.path.join(CSRC, o)
+        cmd = ["hipcc", "-c"] + HIPFLAGS + flags + ["-o", obj, src]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((subprocess.Popen(cmd), cmd))

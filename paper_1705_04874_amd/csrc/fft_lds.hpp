@@ -162,6 +162,20 @@ template <int DIR> struct Dft<5, DIR> {
     }
 };
 
+// The thread's index as a value the compiler cannot trace.  Every pass over
+// columns (the y and z kernels) starts from one: the addresses of a pass's elements are then worked out where they
+// are used.  From threadIdx.x itself they are invariant in a kernel's loops
+// over fields and outputs, and the compiler keeps all of them in registers
+// through the loop (the z operator took 209 VGPRs at 256 x 16 and 156 at
+// 300 x 8, two and three waves per SIMD, against 127 and 70, four and six).
+// The update kernels have no such loop, and k_vel then spills at 5 waves.
+__device__ __forceinline__ int opaque_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // LDS element offset of position i in a pencil: with PAD the row layout gets
 // one spare slot every 16 elements, which spreads power-of-two strides over
 // all LDS banks.
@@ -272,7 +286,7 @@ __device__ __forceinline__ void fft_pass(float2* s, const float2* tw, const Ld& 
     constexpr int Q = (NB + NT - 1) / NT;
     constexpr int TS = N / (NS * R);
     float2 a[Q][R];
-    const int t = threadIdx.x;
+    const int t = COLMAJOR ? opaque_tid() : (int)threadIdx.x;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int b = t + q * NT;
@@ -403,7 +417,7 @@ __device__ __forceinline__ void fft_pass_r(float2* s, const float2* tw, const Ld
     constexpr int Q = (NB + NT - 1) / NT;
     constexpr int TS = N / (NS * R);
     float2 a[Q][R];
-    const int t = threadIdx.x;
+    const int t = COLMAJOR ? opaque_tid() : (int)threadIdx.x;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int b = t + q * NT;
@@ -481,6 +495,18 @@ __device__ __forceinline__ void fft_g2r(float2* s, const float2* tw, const Ld& l
     float2 dummy[1][1];
     FftPassesR<N, 0, false, NPEN, NT, DIR, PS, IS, COLMAJOR, true, false, false, true, Ld, NoSt, float2[1][1],
                ROut, MR>::run(s, tw, ld, NoSt{}, dummy, rout);
+}
+
+// Forward-plan transform whose first pass's inputs are in registers
+// (rin[q][r]: element j + r N / R of butterfly q, R the first radix), outputs
+// to st(pencil, i, v) (no trailing barrier).
+template <int N, int NPEN, int NT, int DIR, int PS, int IS, bool COLMAJOR, class RIn, class St>
+__device__ __forceinline__ void fft_r2g_fwd(float2* s, const float2* tw, RIn& rin, const St& st)
+{
+    static_assert(plan_ok(N), "length must factor into 2, 3 and 5");
+    float2 dummy[1][1];
+    FftPassesR<N, 0, false, NPEN, NT, DIR, PS, IS, COLMAJOR, false, true, true, false, NoLd, St, RIn,
+               float2[1][1]>::run(s, tw, NoLd{}, st, rin, dummy);
 }
 
 // Reversed-plan transform from registers to st(pencil, i, v) (no trailing

@@ -7,12 +7,14 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
+#include <iterator>
 #include <string>
 #include <new>
 #include <vector>
 
 #include "pstd3d.h"
-#include "pstd_kernels.hpp"
+#include "pstd_variants.hpp"
 
 using namespace pstd;
 
@@ -34,209 +36,28 @@ int fail(int code, const std::string& msg)
                         std::string(#expr) + ": " + hipGetErrorString(e_));                 \
     } while (0)
 
-constexpr int NT = 256;
-
-// ---------------------------------------------------------------------------
-// per-length kernel launchers.  Tuning knobs (the autotuner picks one value of
-// each per context): the column-tile width of the y and z kernels and the
-// threads per block of the two update kernels.
-using VelFn = void (*)(dim3, hipStream_t, Geo, Mat, Pml, const float2*, float*, float2*, Rec, float*, const int*,
-                       int*, int, int);
-using StrFn = void (*)(dim3, hipStream_t, Geo, Mat, Pml, const float2*, float*, float2*, Rec, Inj, float*,
-                       const int*, int, int);
-struct XFns {
-    void (*xfwd)(dim3, hipStream_t, Geo, const float2*, const float*, long, float2*, long, SumDesc);
-    void (*xinv)(dim3, hipStream_t, Geo, const float2*, const float2*, float*);
-    int rows;
-};
-struct VelVar {
-    VelFn fn;
-    int nt;
-};
-struct StrVar {
-    StrFn fn;
-    StrFn visc;   // the Kelvin-Voigt variant
-    int nt;
-};
-struct YFns {
-    void (*fwd)(dim3, hipStream_t, Geo, const float2*, float2*, int, int);
-    void (*inv)(dim3, hipStream_t, Geo, const float2*, float2*, int, int);
-    int tile;
-};
-struct ZFns {
-    void (*op)(dim3, hipStream_t, Geo, const float2*, float2*, int, const ZDesc*, int, int);
-    int tile;
-    int nt;     // threads per block
-};
-constexpr int MAX_VARIANTS = 8;
-constexpr int N_TILES = 4;
-constexpr int TILE_CANDIDATES[N_TILES] = {8, 16, 32, 64};
 // input fields per block of the z kernels: one, or every input of the phase
 constexpr int ZF_VALUES[2] = {1, 6};
 
-// threads per block of the update kernels of length N: 128, 256 and 512,
-// none above the cells of a block
-constexpr int nt_candidate(int n, int i)
-{
-    const int cells = rows_for(n) * n;
-    const int c[3] = {128, 256, 512};
-    const int v = c[i];
-    if (v > cells || v % 64 || v > 1024) return 0;
-    for (int j = 0; j < i; ++j)
-        if (c[j] == v) return 0;
-    return v;
-}
-
-template <int N>
-struct Launch {
-    static void xfwd(dim3 gr, hipStream_t st, Geo g, const float2* tw, const float* in, long is, float2* out,
-                     long os, SumDesc sd)
-    {
-        hipLaunchKernelGGL((k_xfwd<N, NT>), gr, dim3(NT), 0, st, g, tw, in, is, out, os, sd);
-    }
-    static void xinv(dim3 gr, hipStream_t st, Geo g, const float2* tw, const float2* in, float* out)
-    {
-        hipLaunchKernelGGL((k_xinv<N, NT>), gr, dim3(NT), 0, st, g, tw, in, out);
-    }
+// One spectrum between the z and the inverse y kernels: from input `in`, stored
+// in derivative slot `slot`, times the z symbol (zplus 0 / 1) or not (-1), and
+// the derivatives formed from it (the last one in its own slot)
+struct Der {
+    int slot, axis, plus;   // axis 0, 1: the symbol that the y kernel applies; 2: none
 };
-
-template <int N, int T>
-struct LaunchX {
-    static void vel(dim3 gr, hipStream_t st, Geo g, Mat m, Pml p, const float2* tw, float* f, float2* s, Rec r,
-                    float* tr, const int* sp, int* sn, int n0, int ldt)
-    {
-        hipLaunchKernelGGL((k_vel<N, T>), gr, dim3(T), 0, st, g, m, p, tw, f, s, r, tr, sp, sn, n0, ldt);
-    }
-    static void str(dim3 gr, hipStream_t st, Geo g, Mat m, Pml p, const float2* tw, float* f, float2* s, Rec r,
-                    Inj in, float* tr, const int* sp, int n0, int ldt)
-    {
-        hipLaunchKernelGGL((k_str<N, T>), gr, dim3(T), 0, st, g, m, p, tw, f, s, r, in, tr, sp, n0, ldt);
-    }
-    static void strv(dim3 gr, hipStream_t st, Geo g, Mat m, Pml p, const float2* tw, float* f, float2* s, Rec r,
-                     Inj in, float* tr, const int* sp, int n0, int ldt)
-    {
-        hipLaunchKernelGGL((k_str<N, T, true>), gr, dim3(T), 0, st, g, m, p, tw, f, s, r, in, tr, sp, n0, ldt);
-    }
-};
-
-template <int N, int I = 0>
-void x_variants(VelVar* v, StrVar* s, int& n)
+void add_spectrum(PhaseDesc& p, int in, int zplus, std::initializer_list<Der> ders)
 {
-    if constexpr (I < 3) {
-        constexpr int T = nt_candidate(N, I);
-        if constexpr (T > 0) {
-            v[n] = VelVar{LaunchX<N, T>::vel, T};
-            s[n] = StrVar{LaunchX<N, T>::str, LaunchX<N, T>::strv, T};
-            ++n;
-        }
-        x_variants<N, I + 1>(v, s, n);
+    const int slot = std::prev(ders.end())->slot;
+    p.zslot[in][p.nz[in]] = slot;
+    p.zplus[in][p.nz[in]++] = zplus;
+    p.ysrc[p.nsrc] = slot;
+    for (const Der& d : ders) {
+        const int o = p.yn[p.nsrc]++;
+        p.yslot[p.nsrc][o] = d.slot;
+        p.yaxis[p.nsrc][o] = d.axis;
+        p.yplus[p.nsrc][o] = d.plus;
     }
-}
-
-template <int N, int TX>
-struct LaunchYZ {
-    static void yf(dim3 gr, hipStream_t st, Geo g, const float2* tw, float2* s, int f0, int nf)
-    {
-        hipLaunchKernelGGL((k_y<N, NT, -1, TX>), gr, dim3(NT), 0, st, g, tw, s, f0, nf);
-    }
-    static void yi(dim3 gr, hipStream_t st, Geo g, const float2* tw, float2* s, int f0, int nf)
-    {
-        hipLaunchKernelGGL((k_y<N, NT, +1, TX>), gr, dim3(NT), 0, st, g, tw, s, f0, nf);
-    }
-    static void z(dim3 gr, hipStream_t st, Geo g, const float2* tw, float2* s, int in0, const ZDesc* zd, int ph,
-                  int fpb)
-    {
-        hipLaunchKernelGGL((k_z<N, NT, TX>), gr, dim3(NT), 0, st, g, tw, s, in0, zd, ph, fpb);
-    }
-    static void z512(dim3 gr, hipStream_t st, Geo g, const float2* tw, float2* s, int in0, const ZDesc* zd, int ph,
-                     int fpb)
-    {
-        hipLaunchKernelGGL((k_z<N, 512, TX, z_maxr(N, TX, 512)>), gr, dim3(512), 0, st, g, tw, s, in0, zd, ph, fpb);
-    }
-};
-
-// the variants of length N: y tiles and z tiles (counts returned)
-template <int N, int I = 0>
-void yz_variants(YFns* y, int& ny, ZFns* z, int& nz)
-{
-    if constexpr (I < N_TILES) {
-        constexpr int TX = TILE_CANDIDATES[I];
-        if constexpr (y_tile_built(N, TX)) y[ny++] = YFns{LaunchYZ<N, TX>::yf, LaunchYZ<N, TX>::yi, TX};
-        if constexpr (z_tile_built(N, TX)) z[nz++] = ZFns{LaunchYZ<N, TX>::z, TX, NT};
-        if constexpr (z512_ok(N, TX)) z[nz++] = ZFns{LaunchYZ<N, TX>::z512, TX, 512};
-        yz_variants<N, I + 1>(y, ny, z, nz);
-    }
-}
-
-// Grid lengths the library is built for (all factor into 2, 3 and 5).
-#define PSTD_LENGTHS(X)                                                                          \
-    X(16) X(20) X(24) X(30) X(32) X(40) X(48) X(60) X(64) X(72) X(75) X(80) X(90) X(96) X(100) X(120) X(125) \
-    X(128) X(144) X(150) X(160) X(180) X(192) X(200) X(240) X(256) X(288) X(300) X(320) X(360)  \
-    X(384) X(400) X(480) X(512)
-
-bool x_fns(int n, XFns* f, VelVar* vv = nullptr, StrVar* sv = nullptr, int* nv = nullptr)
-{
-    VelVar v[3];
-    StrVar t[3];
-    int k = 0;
-    switch (n) {
-#define CASE(N)                                                              \
-    case N:                                                                  \
-        *f = XFns{Launch<N>::xfwd, Launch<N>::xinv, rows_for(N)};            \
-        x_variants<N>(v, t, k);                                              \
-        break;
-        PSTD_LENGTHS(CASE)
-#undef CASE
-    default:
-        return false;
-    }
-    if (nv) {
-        *nv = k;
-        for (int i = 0; i < k; ++i) {
-            vv[i] = v[i];
-            sv[i] = t[i];
-        }
-    }
-    return true;
-}
-
-// all y variants of length n (returns the count; 0: length not built)
-int y_variants(int n, YFns* f)
-{
-    YFns y[MAX_VARIANTS];
-    ZFns z[MAX_VARIANTS];
-    int ny = 0, nz = 0;
-    switch (n) {
-#define CASE(N)                             \
-    case N:                                 \
-        yz_variants<N>(y, ny, z, nz);       \
-        break;
-        PSTD_LENGTHS(CASE)
-#undef CASE
-    default:
-        return 0;
-    }
-    for (int i = 0; i < ny; ++i) f[i] = y[i];
-    return ny;
-}
-
-int z_variants(int n, ZFns* f)
-{
-    YFns y[MAX_VARIANTS];
-    ZFns z[MAX_VARIANTS];
-    int ny = 0, nz = 0;
-    switch (n) {
-#define CASE(N)                             \
-    case N:                                 \
-        yz_variants<N>(y, ny, z, nz);       \
-        break;
-        PSTD_LENGTHS(CASE)
-#undef CASE
-    default:
-        return 0;
-    }
-    for (int i = 0; i < nz; ++i) f[i] = z[i];
-    return nz;
+    ++p.nsrc;
 }
 
 // V phase: stress spectra (sxx, syy, szz, sxy, sxz, syz) -> 9 derivatives,
@@ -245,21 +66,14 @@ PhaseDesc phase_v()
 {
     PhaseDesc p{};
     p.nin = 6;
-    auto set = [&](int in, int o, int idx, int axis, int plus) {
-        p.oidx[in][o] = idx;
-        p.axis[in][o] = axis;
-        p.plus[in][o] = plus;
-        p.nout[in] = o + 1;
-    };
-    set(0, 0, 0, 0, 1);  // Dx+ sxx -> vx(x)
-    set(1, 0, 4, 1, 1);  // Dy+ syy -> vy(y)
-    set(2, 0, 8, 2, 1);  // Dz+ szz -> vz(z)
-    set(3, 0, 1, 1, 0);  // Dy- sxy -> vx(y)
-    set(3, 1, 3, 0, 0);  // Dx- sxy -> vy(x)
-    set(4, 0, 2, 2, 0);  // Dz- sxz -> vx(z)
-    set(4, 1, 6, 0, 0);  // Dx- sxz -> vz(x)
-    set(5, 0, 5, 2, 0);  // Dz- syz -> vy(z)
-    set(5, 1, 7, 1, 0);  // Dy- syz -> vz(y)
+    add_spectrum(p, 0, -1, {{0, 0, 1}});              // Dx+ sxx -> vx(x)
+    add_spectrum(p, 1, -1, {{4, 1, 1}});              // Dy+ syy -> vy(y)
+    add_spectrum(p, 2, 1, {{8, 2, 0}});               // Dz+ szz -> vz(z)
+    add_spectrum(p, 3, -1, {{1, 1, 0}, {3, 0, 0}});   // Dy- sxy -> vx(y), Dx- sxy -> vy(x)
+    add_spectrum(p, 4, -1, {{6, 0, 0}});              // Dx- sxz -> vz(x)
+    add_spectrum(p, 4, 0, {{2, 2, 0}});               // Dz- sxz -> vx(z)
+    add_spectrum(p, 5, -1, {{7, 1, 0}});              // Dy- syz -> vz(y)
+    add_spectrum(p, 5, 0, {{5, 2, 0}});               // Dz- syz -> vy(z)
     return p;
 }
 
@@ -268,22 +82,26 @@ PhaseDesc phase_s()
 {
     PhaseDesc p{};
     p.nin = 3;
-    auto set = [&](int in, int o, int idx, int axis, int plus) {
-        p.oidx[in][o] = idx;
-        p.axis[in][o] = axis;
-        p.plus[in][o] = plus;
-        p.nout[in] = o + 1;
-    };
-    set(0, 0, 0, 0, 0);  // Dx- vx
-    set(0, 1, 3, 1, 1);  // Dy+ vx
-    set(0, 2, 5, 2, 1);  // Dz+ vx
-    set(1, 0, 1, 1, 0);  // Dy- vy
-    set(1, 1, 4, 0, 1);  // Dx+ vy
-    set(1, 2, 7, 2, 1);  // Dz+ vy
-    set(2, 0, 2, 2, 0);  // Dz- vz
-    set(2, 1, 6, 0, 1);  // Dx+ vz
-    set(2, 2, 8, 1, 1);  // Dy+ vz
+    add_spectrum(p, 0, -1, {{3, 1, 1}, {0, 0, 0}});   // Dy+ vx, Dx- vx
+    add_spectrum(p, 0, 1, {{5, 2, 0}});               // Dz+ vx
+    add_spectrum(p, 1, -1, {{4, 0, 1}, {1, 1, 0}});   // Dx+ vy, Dy- vy
+    add_spectrum(p, 1, 1, {{7, 2, 0}});               // Dz+ vy
+    add_spectrum(p, 2, -1, {{8, 1, 1}, {6, 0, 1}});   // Dy+ vz, Dx+ vz
+    add_spectrum(p, 2, 0, {{2, 2, 0}});               // Dz- vz
     return p;
+}
+
+// spectra that the inverse y kernel reads, per phase (velocity, stress)
+constexpr int NSRC[2] = {8, 6};
+
+// non-finite check on sampled trace values: flag = 1 if any is not finite
+__global__ void k_check_finite(const float* __restrict__ tr, long n, int* __restrict__ flag)
+{
+    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    long stride = (long)gridDim.x * blockDim.x;
+    int bad = 0;
+    for (; i < n; i += stride) bad |= !isfinite(tr[i]);
+    if (bad) *flag = 1;
 }
 
 template <class T>
@@ -583,6 +401,11 @@ int build_model(pstd3d_ctx* c, const pstd3d_model* m)
         c->P.fhi[d] = one ? hi : -1;
     }
 
+    // cos and sin of multiples of pi / 2 come out as 1e-16 where they are zero;
+    // kept, the products with them are as good as lost (denormal for fields
+    // below 1e-22) but decide ties in the sums they enter, so that a source of
+    // twice the moment would not give exactly twice the traces
+    auto snap = [](double v) { return std::fabs(v) < 1e-15 ? 0.0 : v; };
     // twiddles exp(-2 pi i e / N) per axis
     std::vector<float2> ht;
     size_t toff[3];
@@ -590,7 +413,7 @@ int build_model(pstd3d_ctx* c, const pstd3d_model* m)
         toff[d] = ht.size();
         for (int e = 0; e < N[d]; ++e) {
             const double a = -2.0 * M_PI * (double)e / N[d];
-            ht.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
+            ht.push_back(make_float2((float)snap(std::cos(a)), (float)snap(std::sin(a))));
         }
     }
     rc = dev_upload(&c->tw, ht);
@@ -614,7 +437,7 @@ int build_model(pstd3d_ctx* c, const pstd3d_model* m)
                 const double k = kval(mi, N[d], c->h[d]);
                 const double a = (plus ? 0.5 : -0.5) * k * c->h[d];
                 // i k (cos a + i sin a) = (-k sin a, k cos a)
-                hs.push_back(make_float2((float)(-k * std::sin(a)), (float)(k * std::cos(a))));
+                hs.push_back(make_float2((float)(-k * snap(std::sin(a))), (float)(k * snap(std::cos(a)))));
             }
         }
     rc = dev_upload(&c->sym, hs);
@@ -747,7 +570,7 @@ void enqueue_step(pstd3d_ctx* c, hipStream_t st, float* traces, int n0, int ldt,
     c->zf.op(dim3(tzn, g.ny, S * ((6 + fpb - 1) / fpb)), st, g, c->twz, c->spec, 0, c->zdesc, 0, fpb);
     c->ev_end(e, st);
     e = c->ev_begin(PSTD_K_YINV_V, st);
-    c->yf.inv(dim3(tyn, g.nz, S * 9), st, g, c->twy, c->spec, 9, 9);
+    c->yf.inv(dim3(tyn, g.nz, S * NSRC[0]), st, g, c->twy, c->spec, c->zdesc, 0, NSRC[0]);
     c->ev_end(e, st);
     e = c->ev_begin(PSTD_K_VEL, st);
     c->vel.fn(gx, st, g, c->M, c->P, c->twx, c->fields, c->spec, rec_of(c), traces, cur, nxt, n0, ldt);
@@ -760,7 +583,7 @@ void enqueue_step(pstd3d_ctx* c, hipStream_t st, float* traces, int n0, int ldt,
     c->zf.op(dim3(tzn, g.ny, S * ((3 + fpb - 1) / fpb)), st, g, c->twz, c->spec, 6, c->zdesc, 1, fpb);
     c->ev_end(e, st);
     e = c->ev_begin(PSTD_K_YINV_S, st);
-    c->yf.inv(dim3(tyn, g.nz, S * 9), st, g, c->twy, c->spec, 9, 9);
+    c->yf.inv(dim3(tyn, g.nz, S * NSRC[1]), st, g, c->twy, c->spec, c->zdesc, 1, NSRC[1]);
     c->ev_end(e, st);
     e = c->ev_begin(PSTD_K_STR, st);
     c->str_fn(c->str)(gx, st, g, c->M, c->P, c->twx, c->fields, c->spec, rec_of(c), inj_of(c), traces, cur, n0,
@@ -770,10 +593,8 @@ void enqueue_step(pstd3d_ctx* c, hipStream_t st, float* traces, int n0, int ldt,
 
 bool len_ok(int n)
 {
-    XFns a;
-    YFns y[MAX_VARIANTS];
-    ZFns z[MAX_VARIANTS];
-    return x_fns(n, &a) && y_variants(n, y) > 0 && z_variants(n, z) > 0;
+    Variants v;
+    return find_variants(n, &v) && v.ny > 0 && v.nz > 0;
 }
 
 // variant used before (or without) tuning: tile 16 and 256 threads where
@@ -838,7 +659,8 @@ int autotune(pstd3d_ctx* c)
             if (k == PSTD_TUNE_Y) {
                 const YFns v = c->yv[i];
                 const int tyn = (g.nxm + v.tile - 1) / v.tile + g.has_nyq;
-                e = timed([&] { v.inv(dim3(tyn, g.nz, S * 9), nullptr, g, c->twy, c->spec, 9, 9); }, &c->tune_us[k][i]);
+                e = timed([&] { v.inv(dim3(tyn, g.nz, S * NSRC[0]), nullptr, g, c->twy, c->spec, c->zdesc, 0, NSRC[0]); },
+                          &c->tune_us[k][i]);
             } else if (k == PSTD_TUNE_Z || k == PSTD_TUNE_ZT || k == PSTD_TUNE_ZF) {
                 // the velocity phase's z operator; the other two z knobs at
                 // their current choice (the tile knob is tuned first)
@@ -976,8 +798,14 @@ int pstd3d_create(const pstd3d_model* m, const double d[3], double dt, const pst
     c->kspace = m->kspace ? 1 : 0;
     c->n_rec = m->n_rec;
     (void)hipGetDevice(&c->device);
-    c->nvar[PSTD_TUNE_Y] = y_variants(ny, c->yv);
-    c->nzv = z_variants(nz, c->zv);
+    Variants vx, vy, vz;
+    find_variants(nx, &vx);
+    find_variants(ny, &vy);
+    find_variants(nz, &vz);
+    c->nvar[PSTD_TUNE_Y] = vy.ny;
+    std::copy(vy.y, vy.y + vy.ny, c->yv);
+    c->nzv = vz.nz;
+    std::copy(vz.z, vz.z + vz.nz, c->zv);
     for (int i = 0; i < c->nzv; ++i) {
         bool seen_t = false, seen_n = false;
         for (int j = 0; j < c->nvar[PSTD_TUNE_Z]; ++j) seen_t = seen_t || c->ztile[j] == c->zv[i].tile;
@@ -986,8 +814,10 @@ int pstd3d_create(const pstd3d_model* m, const double d[3], double dt, const pst
         if (!seen_n) c->znt[c->nvar[PSTD_TUNE_ZT]++] = c->zv[i].nt;
     }
     c->nvar[PSTD_TUNE_ZF] = 2;
-    x_fns(nx, &c->xf, c->velv, c->strv, &c->nvar[PSTD_TUNE_VEL]);
-    c->nvar[PSTD_TUNE_STR] = c->nvar[PSTD_TUNE_VEL];
+    c->xf = vx.x;
+    std::copy(vx.vel, vx.vel + vx.nx, c->velv);
+    std::copy(vx.str, vx.str + vx.nx, c->strv);
+    c->nvar[PSTD_TUNE_VEL] = c->nvar[PSTD_TUNE_STR] = vx.nx;
     for (int k = 0; k < PSTD_TUNE_COUNT; ++k) c->sel[k] = default_variant(c, k);
     c->apply();
     Geo& g = c->g;
@@ -1006,6 +836,13 @@ int pstd3d_create(const pstd3d_model* m, const double d[3], double dt, const pst
     g.fstride = 24 * n;
     g.sstride = 18 * g.nspec;
     int rc = build_model(c, m);
+    // load the kernels of the three lengths now: a group's code object is
+    // loaded on first use, which may not happen under stream capture
+    for (const void* k : {vx.probe, vy.probe, vz.probe}) {
+        hipFuncAttributes attr;
+        const hipError_t e = rc ? hipSuccess : hipFuncGetAttributes(&attr, k);
+        if (e != hipSuccess) rc = fail(PSTD_EDEVICE, std::string("kernels of a grid length: ") + hipGetErrorString(e));
+    }
     if (rc) {
         delete c;
         return rc;
@@ -1403,7 +1240,7 @@ int pstd3d_derivs(pstd3d_ctx* c, int phase, const float* in_dev, float* out_dev,
     c->yf.fwd(dim3(tyn, g.nz, sd.nf), st, g, c->twy, c->spec, in0, sd.nf);
     c->zf.op(dim3(tzn, g.ny, (sd.nf + c->zfpb - 1) / c->zfpb), st, g, c->twz, c->spec, in0, c->zdesc, phase,
              c->zfpb);
-    c->yf.inv(dim3(tyn, g.nz, 9), st, g, c->twy, c->spec, 9, 9);
+    c->yf.inv(dim3(tyn, g.nz, NSRC[phase]), st, g, c->twy, c->spec, c->zdesc, phase, NSRC[phase]);
     c->xf.xinv(gx, st, g, c->twx, c->spec + 9 * g.nspec, out_dev);
     // the stress spectra are part of the state between steps: rebuild them
     enqueue_restore_spectra(c, st);

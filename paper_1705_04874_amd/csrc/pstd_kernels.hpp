@@ -77,13 +77,25 @@ struct Inj {
     int nt_w;
 };
 
-// Outputs of the z kernel: each input spectrum feeds up to three derivatives.
+// How a phase's derivatives are formed.  D_d f = IFFT[i k_d e^{..} kappa FFT f]:
+// kappa couples the axes and is applied where the full spectrum is at hand, in
+// the z kernel; the symbol of one axis only needs that axis in the spectral
+// domain.  The z kernel therefore writes at most two spectra per input, kappa f
+// (which serves the x and the y derivative: the inverse y transform multiplies
+// its input by the y or the x symbol) and, where the input has a z derivative,
+// kappa times the z symbol: 8 instead of 9 spectra in the velocity phase, 6
+// instead of 9 in the stress phase.
 struct PhaseDesc {
     int nin;
-    int nout[6];
-    int oidx[6][3];
-    int axis[6][3];
-    int plus[6][3];     // 1: D+, 0: D-
+    int nz[6];          // z kernel outputs of each input
+    int zslot[6][2];    // derivative slot each is stored in
+    int zplus[6][2];    // -1: kappa alone, 0 / 1: times the D- / D+ z symbol
+    int nsrc;           // spectra that the inverse y kernel reads
+    int ysrc[8];        // their slots
+    int yn[8];          // derivatives formed from each (the last one in place)
+    int yslot[8][2];
+    int yaxis[8][2];    // symbol applied: 0 x, 1 y, 2 none
+    int yplus[8][2];    // 1: D+, 0: D-
 };
 
 struct Ops {
@@ -131,6 +143,9 @@ __device__ __forceinline__ float2 gld(const float2* p)
 // the blocks per CU, against 64-byte instead of 128-byte row segments).
 constexpr bool y_tile_ok(int n, int tx) { return (long)n * (tx + 1) * 8 + n * 8 <= 65536; }
 constexpr bool z_tile_ok(int n, int tx) { return n * tx <= 16 * 256 && (long)n * (tx + 1) * 8 + 3L * n * 8 <= 65536; }
+// threads per block of the y kernels: 512 where the tile's LDS leaves room for
+// only two blocks per compute unit
+constexpr int y_threads(int n, int tx) { return (long)n * (tx + 2) * 8 > 40960 ? 512 : 256; }
 constexpr bool y_tile_built(int n, int tx) { return y_tile_ok(n, tx) && (tx != 8 || !y_tile_ok(n, 16)); }
 constexpr bool z_tile_built(int n, int tx) { return z_tile_ok(n, tx); }
 
@@ -645,7 +660,7 @@ __global__ __launch_bounds__(NT) void k_xinv(Geo g, const float2* __restrict__ t
 // Column tile of a y or z transform: element (column c, position i) is at
 // base[c * cs + i * is]; columns c >= ncol are outside the array.
 struct Tile {
-    float2* __restrict__ base;
+    float2* base;
     long cs, is;
     int ncol;
     // columns past the array read the last column (unconditional load, no
@@ -661,43 +676,127 @@ struct Tile {
     }
 };
 
-// y FFT (forward or inverse) of `nf` spectra starting at field f0, in place.
+// Column tile of plane z (main tiles) or of the Nyquist pencils; false: none
+template <int NY, int TX>
+__device__ __forceinline__ bool y_tile(const Geo& g, long& off, long& cs, long& is, int& ncol)
+{
+    const int tmain = (g.nxm + TX - 1) / TX;
+    if ((int)blockIdx.x < tmain) {
+        const int kx0 = blockIdx.x * TX;
+        off = (long)blockIdx.y * NY * g.ldx + kx0;
+        cs = 1;
+        is = g.ldx;
+        ncol = min(TX, g.nxm - kx0);
+        return true;
+    }
+    const int z0 = blockIdx.y * TX;
+    off = g.nqoff + (long)z0 * NY;
+    cs = NY;
+    is = 1;
+    ncol = min(TX, g.nz - z0);
+    return z0 < g.nz;
+}
+
+// forward y FFT of `nf` spectra starting at field f0, in place.
 // grid: (main tiles + Nyquist tile, nz, shots * nf).  Main tile bx covers
 // columns [TX bx, TX bx + TX) of plane z = by; the Nyquist tile covers the
 // Nyquist pencils of planes [TX by, TX by + TX).
-template <int NY, int NT, int DIR, int TX>
+template <int NY, int NT, int TX>
 __global__ __launch_bounds__(NT) void k_y(Geo g, const float2* __restrict__ twy, float2* __restrict__ spec,
                                           int f0, int nf)
 {
     constexpr int IS = TX + 1;
     __shared__ float2 s[NY * IS];
     __shared__ float2 tw[NY];
-    const int tmain = (g.nxm + TX - 1) / TX;
     const int shot = blockIdx.z / nf, f = f0 + blockIdx.z % nf;
-    float2* __restrict__ fb = spec + (long)shot * g.sstride + (long)f * g.nspec;
-    Tile t;
-    if ((int)blockIdx.x < tmain) {
-        const int kx0 = blockIdx.x * TX;
-        t = Tile{fb + (long)blockIdx.y * NY * g.ldx + kx0, 1, g.ldx, min(TX, g.nxm - kx0)};
-    } else {
-        const int z0 = blockIdx.y * TX;
-        if (z0 >= g.nz) return;
-        t = Tile{fb + g.nqoff + (long)z0 * NY, NY, 1, min(TX, g.nz - z0)};
-    }
+    long off, cs, is;
+    int ncol;
+    if (!y_tile<NY, TX>(g, off, cs, is, ncol)) return;
+    const Tile t{spec + (long)shot * g.sstride + (long)f * g.nspec + off, cs, is, ncol};
     for (int i = threadIdx.x; i < NY; i += NT) tw[i] = twy[i];
-    fft_ld<NY, TX, NT, DIR, 1, IS, true, true>(s, tw, t, t);
+    fft_ld<NY, TX, NT, -1, 1, IS, true, true>(s, tw, t, t);
 }
 
-// z FFT, multiply by the staggered derivative symbols and kappa, inverse z
-// FFT.  grid: (main tiles + Nyquist tile, ny, shots * groups).  Main tile bx
+// Loader of the inverse y transform: a column tile times the y symbol (ysym;
+// from LDS, or global memory if it does not fit) or a value per column
+template <bool LDS>
+struct TileSym {
+    Tile t;
+    const float2* sy;
+    float2 k;
+    float sgn;
+    bool ysym;
+    __device__ float2 operator()(int c, int i) const
+    {
+        const float2 v = t(c, i);
+        const float2 y = LDS ? sy[i] : gld(sy + i);
+        return c_mul(ysym ? make_float2(sgn * y.x, y.y) : k, v);
+    }
+};
+
+// inverse y FFTs of one phase, forming the x and y derivatives: a block takes a
+// tile of one of the phase's nsrc spectra and, for each derivative formed from
+// it, loads the first pass's butterflies, multiplies them by the y symbol, the
+// x symbol (one value per column) or nothing and transforms.  A second
+// derivative finds the tile in the L2 (kept in registers through the first
+// transform it took 256 of them at length 384 and 600 us).  At 384 x 384 x 256:
+// 550 and 517 us for 17 and 15 spectra read or written, against 511 and 523 for
+// 18 when the z kernel wrote all nine derivatives; the z kernel's part is
+// 515 -> 488 and 420 -> 298 us.
+// Every element is read before the first store, and the last derivative goes
+// back in place.  grid: (main tiles + Nyquist tile, nz, shots * nsrc).
+template <int NY, int NT, int TX>
+__global__ __launch_bounds__(NT) void k_yinv(Geo g, const float2* __restrict__ twy, float2* spec,
+                                             const ZDesc* __restrict__ zd, int phase, int nsrc)
+{
+    constexpr int IS = TX + 1;
+    constexpr int R0 = plan_radix(NY, 0), Q = (TX * (NY / R0) + NT - 1) / NT;
+    // the y symbol goes to LDS where it fits beside the tile
+    constexpr bool SYL = (long)NY * (IS + 2) * 8 <= 65536;
+    static_assert(NT % TX == 0, "a thread keeps its column");
+    __shared__ float2 s[NY * IS];
+    __shared__ float2 tw[NY];
+    __shared__ float2 sy[SYL ? NY : 1];
+    const PhaseDesc& ph = zd->ph[phase];
+    const int shot = blockIdx.z / nsrc, src = blockIdx.z % nsrc;
+    long off, cs, is;
+    int ncol;
+    if (!y_tile<NY, TX>(g, off, cs, is, ncol)) return;
+    float2* D9 = spec + (long)shot * g.sstride + 9 * g.nspec + off;
+    for (int i = threadIdx.x; i < NY; i += NT) {
+        tw[i] = twy[i];
+        if constexpr (SYL) sy[i] = gld(zd->ops.sym[1][1] + i);
+    }
+    // x symbol of this thread's column (the Nyquist pencils: that of nx / 2)
+    const int kx = cs == 1 ? blockIdx.x * TX + min((int)threadIdx.x % TX, ncol - 1) : g.nx / 2;
+    const float2 sx = gld(zd->ops.sym[0][1] + kx);
+    const int n = ph.yn[src];
+    for (int o = 0; o < n; ++o) {
+        // an offset the compiler cannot see through: without it the addresses
+        // of every element are worked out before the loop and kept
+        long zero = 0;
+        asm volatile("" : "+s"(zero));
+        const Tile in{D9 + ph.ysrc[src] * g.nspec + zero, cs, is + zero, ncol};
+        const Tile out{D9 + ph.yslot[src][o] * g.nspec, cs, is + zero, ncol};
+        const int axis = ph.yaxis[src][o];
+        // D- is D+ with the real part negated: i k e^{-i k h/2} = (k sin, k cos)
+        const float sgn = ph.yplus[src][o] ? 1.f : -1.f;
+        const float2 k = axis == 0 ? make_float2(sgn * sx.x, sx.y) : make_float2(1.f, 0.f);
+        __syncthreads();   // tw and sy staged; s was read by the previous last pass
+        fft_ld<NY, TX, NT, +1, 1, IS, true, true>(s, tw, TileSym<SYL>{in, SYL ? sy : zd->ops.sym[1][1] + zero, k, sgn, axis == 1}, out);
+    }
+}
+
+// z FFT, multiply by kappa and, for the z derivatives, the staggered symbol,
+// inverse z FFT.  grid: (main tiles + Nyquist tile, ny, shots * groups).  Main tile bx
 // covers columns [TX bx, +TX) of row ky = by; the Nyquist tile covers the
 // Nyquist pencils of rows [TX by, +TX).  A block takes the input spectra
 // [fpb g, fpb g + fpb) of its shot (g = blockIdx.z % groups), so that with
 // fpb >= the phase's inputs one block applies its tile's kappa and symbols
 // (loaded once) to every input field in turn.  For each input it reads
-// spectrum `in0 + input`, writes the derivative spectra (9 + output index):
-// the forward spectrum stays in registers, each output is multiplied there
-// and inverted with the reversed radix plan.  MR caps the radix of the plan
+// spectrum `in0 + input` and writes one or two spectra (9 + slot, see
+// PhaseDesc): the forward spectrum stays in registers, each output is
+// multiplied there and inverted with the reversed radix plan.  MR caps the radix of the plan
 // (16, or 8 for the 512-thread variants, whose threads then all take a
 // butterfly of the first pass).
 template <int NZ, int NT, int TX, int MR = 16>
@@ -709,14 +808,13 @@ __global__ __launch_bounds__(NT) void k_z(Geo g, const float2* __restrict__ twz,
     constexpr int IS = TX + 1;
     using RS = RegShape<NZ, TX, NT, MR>;
     constexpr int RL = RS::RL, QL = RS::QL;
-    // LDS: the tile, the twiddles, and the D+ symbols along z and of the tile's
-    // columns (D- is D+ with the real part negated: i k e^{-i k h/2} =
-    // (k sin, k cos) against (-k sin, k cos)); kept under 40 KB at length 256
-    // so that four blocks share a CU
+    // LDS: the tile, the twiddles, and the D+ symbol along z (D- is D+ with the
+    // real part negated: i k e^{-i k h/2} = (k sin, k cos) against
+    // (-k sin, k cos)); kept under 40 KB at length 256 so that four blocks
+    // share a CU
     __shared__ float2 s[NZ * IS];
     __shared__ float2 tw[NZ];
     __shared__ float2 symz[NZ];
-    __shared__ float2 symc[2][TX];
     __shared__ float kxy2[TX];
     // the forward spectrum is reused by every output of the input field; kept
     // in registers it stays live through the inverse transforms (about a
@@ -761,12 +859,6 @@ __global__ __launch_bounds__(NT) void k_z(Geo g, const float2* __restrict__ twz,
             const int c = min(i, ncol - 1);
             kxy2[i] = gld(ops.k2[0] + kx0 + kxc * c) + gld(ops.k2[1] + ky0 + kyc * c);
         }
-    // x and y D+ symbols of this tile's columns (main tiles: kx0 + c and ky0;
-    // Nyquist tile: nx/2 and ky0 + c), so that the multiply loop reads LDS only
-    for (int i = threadIdx.x; i < 2 * TX; i += NT) {
-        const int ax = i / TX, c = min(i % TX, ncol - 1);
-        symc[ax][i % TX] = gld(ops.sym[ax][1] + (ax == 0 ? kx0 + kxc * c : ky0 + kyc * c));
-    }
     __syncthreads();
     // kappa of the elements this thread multiplies, once for all the block's inputs
     float kr[QL][RL];
@@ -801,11 +893,8 @@ __global__ __launch_bounds__(NT) void k_z(Geo g, const float2* __restrict__ twz,
 #pragma unroll
                 for (int r = 0; r < RL; ++r) xs[(q * RL + r) * NT + threadIdx.x] = X[q][r];
         }
-        for (int o = 0; o < ph.nout[fi]; ++o) {
-            const int axis = ph.axis[fi][o], plus = ph.plus[fi][o];
-            // symbol table of this output: along z indexed by z, along x or y by column
-            const float2* tab = axis == 2 ? symz : symc[axis];
-            const bool byz = axis == 2;
+        for (int o = 0; o < ph.nz[fi]; ++o) {
+            const int plus = ph.zplus[fi][o];
             const float sgn = plus ? 1.f : -1.f;
             float2 Y[QL][RL];
 #pragma unroll
@@ -814,13 +903,15 @@ __global__ __launch_bounds__(NT) void k_z(Geo g, const float2* __restrict__ twz,
                 for (int r = 0; r < RL; ++r) {
                     int c, z;
                     reg_coords<NZ, RL, TX, NT, true>(q, r, c, z);
-                    const float2 s1 = tab[byz ? z : c];
-                    const float2 sv = make_float2(sgn * s1.x, s1.y);
-                    const float2 xv = STASH ? xs[(q * RL + r) * NT + threadIdx.x] : X[q][r];
-                    Y[q][r] = c_scale(c_mul(sv, xv), kr[q][r]);
+                    float2 xv = STASH ? xs[(q * RL + r) * NT + threadIdx.x] : X[q][r];
+                    if (plus >= 0) {   // the same for the whole block
+                        const float2 s1 = symz[z];
+                        xv = c_mul(make_float2(sgn * s1.x, s1.y), xv);
+                    }
+                    Y[q][r] = c_scale(xv, kr[q][r]);
                 }
             __syncthreads();   // s was read by the previous pass
-            const Tile out{sb + (long)(9 + ph.oidx[fi][o]) * g.nspec + off, 1, zs, ncol};
+            const Tile out{sb + (long)(9 + ph.zslot[fi][o]) * g.nspec + off, 1, zs, ncol};
             fft_r2g<NZ, TX, NT, +1, 1, IS, true, float2[QL][RL], Tile, MR>(s, tw, Y, out);
         }
     }
@@ -831,15 +922,5 @@ __global__ __launch_bounds__(NT) void k_z(Geo g, const float2* __restrict__ twz,
 constexpr int z_maxr(int n, int tx, int nt) { return tx * (n / 16) >= nt ? 16 : 8; }
 // at least four values per thread and a radix-8 (or 16) first pass
 constexpr bool z512_ok(int n, int tx) { return z_tile_ok(n, tx) && n * tx >= 4 * 512 && n % 8 == 0 && tx * (n / 8) >= 512; }
-
-// non-finite check on sampled trace values: flag = 1 if any is not finite
-__global__ void k_check_finite(const float* __restrict__ tr, long n, int* __restrict__ flag)
-{
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    long stride = (long)gridDim.x * blockDim.x;
-    int bad = 0;
-    for (; i < n; i += stride) bad |= !isfinite(tr[i]);
-    if (bad) *flag = 1;
-}
 
 }  // namespace pstd

@@ -92,6 +92,38 @@ def test_derivatives_at_large_lengths(B, shape):
         assert e < 2e-5, (o, e)
 
 
+@pytest.mark.parametrize("ny", [16, 75, 144, 240, 384])
+def test_derivatives_for_every_y_tile(B, ny):
+    """Both phases' nine derivatives with every built y tile forced (the inverse
+    y kernel forms the x and y derivatives of one spectrum in turn, the second
+    in place; 512 threads where the tile is large; at 240 the widest tile leaves
+    no room for the symbol in LDS), with and without a Nyquist plane, against
+    the oracle (FP32 transforms: 2e-5)."""
+    import torch
+    h, dt = (10.0, 12.0, 9.0), 0.8e-3
+    rng = np.random.default_rng(8)
+    tables = [[(0, +1, 0), (1, -1, 3), (2, -1, 4), (0, -1, 3), (1, +1, 1), (2, -1, 5), (0, -1, 4), (1, -1, 5),
+               (2, +1, 2)],
+              [(0, -1, 0), (1, -1, 1), (2, -1, 2), (1, +1, 0), (0, +1, 1), (2, +1, 0), (0, +1, 2), (2, +1, 1),
+               (1, +1, 2)]]
+    for nx in (20, 75):
+        shape = (16, ny, nx)
+        vp = 2500 + 500 * rng.random(shape)
+        s = B.Solver(vp, vp / 1.8, 310 * vp ** 0.25, h, dt, pml=4, kspace=1)
+        s.set_sources([0, 0], np.zeros((0, 3)), np.zeros((0, 6)), np.zeros((0, 1)))
+        f = rng.standard_normal((6,) + shape)
+        refs = [[oracle.deriv(f[src], axis, sign, h=h, kspace=1, c_ref=vp.max(), dt=dt) for axis, sign, src in t]
+                for t in tables]
+        for tile in s.tuning()["y_tile_candidates"]:
+            s.set_tuning(y_tile=tile)
+            for phase, nin in ((0, 6), (1, 3)):
+                got = s.derivs(phase, torch.from_numpy(f[:nin].astype(np.float32)).cuda()).cpu().numpy()
+                for o in range(9):
+                    e = np.linalg.norm(got[o] - refs[phase][o]) / np.linalg.norm(refs[phase][o])
+                    assert e < 2e-5, (nx, tile, phase, o, e)
+        s.close()
+
+
 @pytest.fixture(scope="module")
 def layered384_runs(B):
     nt = 1000
