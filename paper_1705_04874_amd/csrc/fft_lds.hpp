@@ -256,7 +256,9 @@ __host__ __device__ constexpr int plan_ns_rev(int n, int p, int mr = 16)
 
 // Loaders that split into fetch (loads only) and finish (arithmetic on the
 // loaded values) declare TWO_PHASE; a pass then issues all of a butterfly's
-// loads before any of the arithmetic.
+// loads before any of the arithmetic.  begin<R>(pencil, j) works out what the
+// elements j + r M of one radix-R butterfly share; fetch and finish take r, a
+// constant once the loop over it is unrolled.
 template <class Ld, class = void>
 struct TwoPhase {
     static constexpr bool value = false;
@@ -296,12 +298,13 @@ __device__ __forceinline__ void fft_pass(float2* s, const float2* tw, const Ld& 
             const int k = j % NS;
             if constexpr (FROM_G && two_phase<Ld>()) {
                 // every load of the butterfly first, then the arithmetic on them
+                const auto at = ld.template begin<R>(pen, j);
                 typename Ld::Raw raw[R];
 #pragma unroll
-                for (int r = 0; r < R; ++r) raw[r] = ld.fetch(pen, j + r * M);
+                for (int r = 0; r < R; ++r) raw[r] = ld.template fetch<R>(at, j, r);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int r = 0; r < R; ++r) a[q][r] = ld.finish(raw[r], j + r * M);
+                for (int r = 0; r < R; ++r) a[q][r] = ld.template finish<R>(raw[r], j, r);
             } else {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
@@ -495,18 +498,6 @@ __device__ __forceinline__ void fft_g2r(float2* s, const float2* tw, const Ld& l
     float2 dummy[1][1];
     FftPassesR<N, 0, false, NPEN, NT, DIR, PS, IS, COLMAJOR, true, false, false, true, Ld, NoSt, float2[1][1],
                ROut, MR>::run(s, tw, ld, NoSt{}, dummy, rout);
-}
-
-// Forward-plan transform whose first pass's inputs are in registers
-// (rin[q][r]: element j + r N / R of butterfly q, R the first radix), outputs
-// to st(pencil, i, v) (no trailing barrier).
-template <int N, int NPEN, int NT, int DIR, int PS, int IS, bool COLMAJOR, class RIn, class St>
-__device__ __forceinline__ void fft_r2g_fwd(float2* s, const float2* tw, RIn& rin, const St& st)
-{
-    static_assert(plan_ok(N), "length must factor into 2, 3 and 5");
-    float2 dummy[1][1];
-    FftPassesR<N, 0, false, NPEN, NT, DIR, PS, IS, COLMAJOR, false, true, true, false, NoLd, St, RIn,
-               float2[1][1]>::run(s, tw, NoLd{}, st, rin, dummy);
 }
 
 // Reversed-plan transform from registers to st(pencil, i, v) (no trailing

@@ -11,6 +11,7 @@
 #include <iterator>
 #include <string>
 #include <new>
+#include <tuple>
 #include <vector>
 
 #include "pstd3d.h"
@@ -869,7 +870,7 @@ int pstd3d_set_sources(pstd3d_ctx* c, int n_shots, const int32_t* shot_ofs, cons
             if (!std::isfinite(m6[6 * q + t])) return fail(PSTD_EINVAL, "non-finite moment tensor");
     }
     HIP_TRY(hipSetDevice(c->device));
-    // injection entries per shot: {x, split part, coef, wavelet row}
+    // injection entries per shot: {cell, split part, coef, wavelet row}
     const double dV = c->h[0] * c->h[1] * c->h[2];
     const int nrows = c->g.nrows;
     std::vector<int> ptr((size_t)n_shots * (nrows + 1), 0);
@@ -886,8 +887,8 @@ int pstd3d_set_sources(pstd3d_ctx* c, int n_shots, const int32_t* shot_ofs, cons
                 if (M[cc] == 0.0) continue;
                 const float coef = (float)(-c->dt * weight * M[cc] / dV / 3.0);
                 for (int d = 0; d < 3; ++d) {
-                    int4 e = make_int4(p[0], 3 * cc + d, __builtin_bit_cast(int, coef), q);
-                    es.push_back({(long)p[1] + (long)ny * p[2], e});
+                    const int row = p[1] + ny * p[2];
+                    es.push_back({row, make_int4(row * nx + p[0], 3 * cc + d, __builtin_bit_cast(int, coef), q)});
                 }
             }
             for (int pr = 0; pr < 3; ++pr) {
@@ -900,8 +901,9 @@ int pstd3d_set_sources(pstd3d_ctx* c, int n_shots, const int32_t* shot_ofs, cons
                         ix[a0] = (ix[a0] + o0 + N[a0]) % N[a0];
                         ix[a1] = (ix[a1] + o1 + N[a1]) % N[a1];
                         for (int t = 0; t < 2; ++t) {
-                            int4 e = make_int4(ix[0], 9 + 2 * pr + t, __builtin_bit_cast(int, coef), q);
-                            es.push_back({(long)ix[1] + (long)ny * ix[2], e});
+                            const int row = ix[1] + ny * ix[2];
+                            es.push_back({row, make_int4(row * nx + ix[0], 9 + 2 * pr + t,
+                                                         __builtin_bit_cast(int, coef), q)});
                         }
                     }
             }
@@ -927,7 +929,20 @@ int pstd3d_set_sources(pstd3d_ctx* c, int n_shots, const int32_t* shot_ofs, cons
                         point(pp, M, st[dx + 2] * st[dy + 2] * st[dz + 2], q);
                     }
         }
-        std::stable_sort(es.begin(), es.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
+        // a smoothed couple's stencils overlap: one entry for what a source adds
+        // to one field of one cell (165 entries per row become 79)
+        std::sort(es.begin(), es.end(), [](const auto& a, const auto& b) {
+            return std::tie(a.second.x, a.second.w, a.second.y) < std::tie(b.second.x, b.second.w, b.second.y);
+        });
+        size_t kept = 0;
+        for (size_t i = 0, j; i < es.size(); i = j) {
+            const int4 e = es[i].second;
+            double coef = 0.0;
+            for (j = i; j < es.size() && es[j].second.x == e.x && es[j].second.w == e.w && es[j].second.y == e.y; ++j)
+                coef += __builtin_bit_cast(float, es[j].second.z);
+            es[kept++] = {es[i].first, make_int4(e.x, e.y, __builtin_bit_cast(int, (float)coef), e.w)};
+        }
+        es.resize(kept);
         int* sp = &ptr[(size_t)s * (nrows + 1)];
         const int base = (int)ent.size();
         for (auto& e : es) sp[e.first + 1]++;

@@ -72,7 +72,7 @@ struct Rec {
 
 struct Inj {
     const int* ptr;     // [n_shots][nrows + 1]
-    const int4* ent;    // {x, split field 0..14, coef (float bits), wavelet row}
+    const int4* ent;    // {row nx + x, split field 0..14, coef (float bits), wavelet row}
     const float* wav;   // [n_src_total][nt_w]
     int nt_w;
 };
@@ -156,49 +156,85 @@ __device__ __forceinline__ long spec_idx(const Geo& g, int row, int k)
     return k < g.nxm ? (long)row * g.ldx + k : g.nqoff + row;
 }
 
-// value of real pencil p (= field * ROWS + local row) of a spectrum row.  Rows
-// past the grid (only in the last block of a ragged row count) read the last
-// row instead: their pencils are transformed on their own and never stored,
-// and no branch separates the loads of a pass, so all of them are issued
-// before the first wait
-__device__ __forceinline__ float2 spec_at(const float2* __restrict__ base, const Geo& g, int rows,
-                                          int row0, int p, int k)
-{
-    const int f = p / rows, r = p - f * rows;
-    const int row = min(row0 + r, g.nrows - 1);
-    return base[f * g.nspec + spec_idx(g, row, k)];
-}
-
 // Loader for an inverse x transform: complex pencil q is the Hermitian
 // extension of the half spectra of real pencils 2q and 2q+1 (Z = A + i B), so
-// one complex inverse FFT gives both real rows (as real and imaginary parts).
-// DC and Nyquist keep only their real parts.
+// one complex inverse FFT gives both real rows (as real and imaginary parts;
+// ROWS is even: both are rows of one field).  DC and Nyquist keep only their
+// real parts.  Rows past the grid (only in the last block of a ragged row
+// count) read the last row instead: their pencils are transformed on their own
+// and never stored, and no branch separates the loads of a pass.
+//
+// fetch() loads the two half-spectrum values at k = min(i, NX - i), finish()
+// combines them with w = sign(2 i - NX) (0 at DC and at the Nyquist bin):
+// Z_i = (a.x + w b.y) + i (b.x - w a.y).  In a butterfly of even radix R the
+// elements r < R / 2 lie below NX / 2 and the others above, and DC and Nyquist
+// can only be r = 0 and r = R / 2 of j = 0: the sign is a constant, two
+// addresses per row serve the butterfly with constant offsets, and only one
+// element asks for the Nyquist plane.  (With the index, its half and the sign
+// worked out per element the loads took some 20 instructions each.)
 template <int NX, int ROWS>
 struct HermLoader {
     const float2* __restrict__ src;
     Geo g;
     int row0;
-    // Two phases, so that a pass issues the loads of all its elements before
-    // the first wait: fetch() loads the two half-spectrum values at
-    // k = min(i, NX - i); finish() combines them branch free with
-    // w = sign(2 i - NX) (0 at DC and at the Nyquist bin):
-    // Z_i = (a.x + w b.y) + i (b.x - w a.y)
     static constexpr bool TWO_PHASE = true;
     using Raw = float4;
-    __device__ float4 fetch(int q, int i) const
+    struct At {
+        const float2 *a, *b;     // k = j of the two rows
+        const float2 *ha, *hb;   // k = NX - j (even radix)
+        long nyq;                // Nyquist value of the first row
+        long nstep;              // to that of the second
+    };
+    template <int R>
+    __device__ At begin(int q, int j) const
     {
-        const int k = min(i, NX - i);
-        const float2 a = spec_at(src, g, ROWS, row0, 2 * q, k);
-        const float2 b = spec_at(src, g, ROWS, row0, 2 * q + 1, k);
+        const int f = 2 * q / ROWS, r = 2 * q - f * ROWS;
+        const int ra = min(row0 + r, g.nrows - 1), rb = min(row0 + r + 1, g.nrows - 1);
+        const float2* p = src + (long)f * g.nspec;
+        At t;
+        t.a = p + (long)ra * g.ldx + j;
+        t.b = t.a + (ra == rb ? 0 : g.ldx);
+        t.ha = t.a + (NX - 2 * j);
+        t.hb = t.b + (NX - 2 * j);
+        t.nyq = (long)f * g.nspec + g.nqoff + ra;
+        t.nstep = rb - ra;
+        return t;
+    }
+    template <int R>
+    __device__ float4 fetch(const At& t, int j, int r) const
+    {
+        constexpr int M = NX / R;
+        const float2 *pa, *pb;
+        if (R % 2 == 0) {
+            pa = 2 * r < R ? t.a + r * M : t.ha - r * M;
+            pb = 2 * r < R ? t.b + r * M : t.hb - r * M;
+            if (2 * r == R && j == 0) {
+                pa = src + t.nyq;
+                pb = pa + t.nstep;
+            }
+        } else {
+            // odd radix: NX is odd (no Nyquist plane)
+            const int i = j + r * M, d = min(i, NX - i) - j;
+            pa = t.a + d;
+            pb = t.b + d;
+        }
+        const float2 a = *pa, b = *pb;
         return make_float4(a.x, a.y, b.x, b.y);
     }
-    __device__ float2 finish(float4 v, int i) const
+    template <int R>
+    __device__ float2 finish(float4 v, int j, int r) const
     {
-        const int sg = (2 * i > NX) - (2 * i < NX);
-        const float w = (float)(i == 0 ? 0 : sg);
+        constexpr int M = NX / R;
+        float w;
+        if (R % 2 == 0) {
+            w = 2 * r < R ? -1.f : 1.f;
+            if ((r == 0 || 2 * r == R) && j == 0) w = 0.f;
+        } else {
+            const int i = j + r * M;
+            w = i == 0 ? 0.f : 2 * i > NX ? 1.f : -1.f;
+        }
         return make_float2(fmaf(w, v.w, v.x), fmaf(-w, v.y, v.z));
     }
-    __device__ float2 operator()(int q, int i) const { return finish(fetch(q, i), i); }
 };
 
 // Unpack NPO complex forward transforms of paired real rows into half spectra.
@@ -212,13 +248,10 @@ __device__ __forceinline__ void unstage_r2c(const float2* s, float2* __restrict_
         const float2 zm = s[q * PS + lidx<true>(k == 0 ? 0 : NX - k)];
         const float2 A = make_float2(0.5f * (z.x + zm.x), 0.5f * (z.y - zm.y));
         const float2 B = make_float2(0.5f * (z.y + zm.y), -0.5f * (z.x - zm.x));
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int p = 2 * q + h;
-            const int f = p / ROWS, r = p - f * ROWS;
-            const int row = row0 + r;
-            if (row < g.nrows) dst[f * g.nspec + spec_idx(g, row, k)] = h ? B : A;
-        }
+        const int f = 2 * q / ROWS, row = row0 + 2 * q - f * ROWS;
+        float2* d = dst + (long)f * g.nspec + spec_idx(g, row, k);
+        if (row < g.nrows) d[0] = A;
+        if (row + 1 < g.nrows) d[k < g.nxm ? g.ldx : 1] = B;
     }
 }
 
@@ -235,6 +268,40 @@ __device__ __forceinline__ void pencil_set(float2* s, int p, int x, float v)
 {
     float* f = reinterpret_cast<float*>(s + (p >> 1) * PS + lidx<true>(x));
     f[p & 1] = v;
+}
+
+// Field values by a block-uniform base and a 32-bit byte offset (a field is at
+// most 512^3 floats): the base stays in scalar registers and one vector
+// register addresses a cell in every field, where 64-bit indices cost two or
+// three vector instructions per access.  The empty asm keeps the base a value
+// of its own; otherwise the compiler adds the cell to the first field's address
+// and the field's distance to that, in vector registers.
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) char* scalar_base(T* p)
+{
+    const unsigned long long u = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)u);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(u >> 32));
+    auto b = (__attribute__((address_space(1))) char*)((unsigned long long)hi << 32 | lo);
+    asm("" : "+s"(b));
+    return b;
+}
+__device__ __forceinline__ float ldf(const float* base, unsigned off)
+{
+    return *(const __attribute__((address_space(1))) float*)(scalar_base(base) + off);
+}
+__device__ __forceinline__ void stf(float* base, unsigned off, float v)
+{
+    *(__attribute__((address_space(1))) float*)(scalar_base(base) + off) = v;
+}
+
+// Row r of a block's rows as the thread knows it: where a wave's 64 cells lie in
+// one row (NX a multiple of 64) it is made a scalar, and with it the row's y
+// and z and everything read by them.
+template <int NX>
+__device__ __forceinline__ int wave_row(int r)
+{
+    return NX % 64 == 0 ? __builtin_amdgcn_readfirstlane(r) : r;
 }
 
 // Block -> (shot, first row) of the update kernels.  A batch of shots is
@@ -292,6 +359,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
     float* __restrict__ F = fields + (long)shot * g.fstride;
     const float2* __restrict__ D9 = spec + (long)shot * g.sstride + 9 * g.nspec;
     float2* __restrict__ S3 = spec + (long)shot * g.sstride + 6 * g.nspec;
+    const int e0 = rc.ptr[row0], e1 = rc.ptr[min(row0 + ROWS, g.nrows)];   // receivers, needed last
 
     for (int i = threadIdx.x; i < NX; i += NT) tw[i] = twx[i];
     fft_ld<NX, NPI, NT, +1, PS, 1, false, false, HermLoader<NX, ROWS>, NoSt, true>(s, tw, HermLoader<NX, ROWS>{D9, g, row0}, NoSt{});
@@ -300,16 +368,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
     // base pointer, so interleaved stores would serialise later loads
     float vp[CPT][9], dtr[CPT][3], a[CPT][3][3];
     bool ok[CPT], in[CPT];
-    long cell[CPT];
+    unsigned cell[CPT];   // byte offset
+    const int z0 = row0 / g.ny, y0 = row0 - z0 * g.ny;   // ROWS <= 16 <= ny: at most one step in z
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
         const int c = threadIdx.x + i * NT;
-        const int r = c / NX, x = c - r * NX;
-        const int row = row0 + r;
-        ok[i] = c < ROWS * NX && row < g.nrows;
-        const int rr = ok[i] ? row : row0;
-        const int y = rr % g.ny, z = rr / g.ny;
-        cell[i] = (long)rr * NX + x;
+        const int r = wave_row<NX>(c / NX), x = c - r * NX;
+        ok[i] = c < ROWS * NX && row0 + r < g.nrows;
+        const int rr = ok[i] ? r : 0;
+        const bool up = y0 + rr >= g.ny;
+        const int y = y0 + rr - (up ? g.ny : 0), z = z0 + (up ? 1 : 0);
+        cell[i] = 4u * ((unsigned)(row0 + rr) * NX + x);
         in[i] = undamped(pm, x, y, z);
         const float axi = pm.ai[0][x], axh = pm.ah[0][x];
         const float ayi = pm.ai[1][y], ayh = pm.ah[1][y];
@@ -322,11 +391,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
         a[i][0][0] = axh * byi * bzi; a[i][0][1] = ayi * bxh * bzi; a[i][0][2] = azi * bxh * byi;
         a[i][1][0] = axi * byh * bzi; a[i][1][1] = ayh * bxi * bzi; a[i][1][2] = azi * bxi * byh;
         a[i][2][0] = axi * byi * bzh; a[i][2][1] = ayi * bxi * bzh; a[i][2][2] = azh * bxi * byi;
-        // an undamped cell reads only the first part of each component
+        // an undamped cell reads only the first part of each component (cells
+        // outside the grid read valid ones and store nothing)
 #pragma unroll
-        for (int q = 0; q < 9; ++q) vp[i][q] = ok[i] && (q % 3 == 0 || !in[i]) ? F[(long)q * g.n + cell[i]] : 0.f;
+        for (int comp = 0; comp < 3; ++comp) {
+            vp[i][3 * comp] = ldf(F + 3 * comp * g.n, cell[i]);
+            vp[i][3 * comp + 1] = vp[i][3 * comp + 2] = 0.f;
+            dtr[i][comp] = ldf(m.dtr[comp], cell[i]);
+        }
+        if (!in[i])
 #pragma unroll
-        for (int comp = 0; comp < 3; ++comp) dtr[i][comp] = ok[i] ? m.dtr[comp][cell[i]] : 0.f;
+            for (int q = 0; q < 9; ++q)
+                if (q % 3) vp[i][q] = ldf(F + q * g.n, cell[i]);
     }
 
     float vsum[CPT][3];
@@ -351,8 +427,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
         }
         if (ok[i]) {
 #pragma unroll
-            for (int q = 0; q < 9; ++q)
-                if (q % 3 == 0 || !in[i]) F[(long)q * g.n + cell[i]] = vp[i][q];
+            for (int q = 0; q < 9; q += 3) stf(F + q * g.n, cell[i], vp[i][q]);
+            if (!in[i])
+#pragma unroll
+                for (int q = 0; q < 9; ++q)
+                    if (q % 3) stf(F + q * g.n, cell[i], vp[i][q]);
         }
     }
     __syncthreads();
@@ -367,8 +446,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
     __syncthreads();
     // receivers (vx, vy, vz at their staggered nodes, time (n + 1/2) dt)
     {
-        const int rend = min(row0 + ROWS, g.nrows);
-        const int e0 = rc.ptr[row0], e1 = rc.ptr[rend];
         const int tn = step - n0;
         for (int e = e0 + threadIdx.x; e < e1; e += NT) {
             const int4 q = rc.ent[e];
@@ -386,7 +463,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
 // ---------------------------------------------------------------------------
 // S phase tail: inverse x FFT of the 9 velocity derivatives, stress split-PML
 // update (eq. 2 first line), source injection, receiver p (eq. 3), x FFT of
-// the 6 summed stresses.
+// the 6 summed stresses.  Bound by memory where the grid is large and by the
+// vector pipe below: at 384 x 384 x 256 it moves 5.2 GB in 1.25 ms, and of its
+// instructions more than a third were addresses (2691 vector instructions per
+// thread at 384 with 64-bit indices, a division per cell and a branch per
+// element of the loads, 2120 without the injection loop now).  Velocity and
+// stress update together at 128^3: 158 -> 137 us; with a smoothed source at
+// 125 x 75 x 300 the stress update went from 207 to 100 us.
 // the first split part of a stress component (parts 0-8: three per normal
 // component, 9-14: two per shear component)
 __host__ __device__ constexpr bool first_part(int q) { return q < 9 ? q % 3 == 0 : (q - 9) % 2 == 0; }
@@ -419,6 +502,7 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
     float2* __restrict__ S6 = spec + (long)shot * g.sstride;
     const int step = *stepp;
     const int* __restrict__ iptr = inj.ptr + (long)shot * (g.nrows + 1);
+    const int e0 = rc.ptr[row0], e1 = rc.ptr[min(row0 + ROWS, g.nrows)];   // receivers, needed last
 
     for (int i = threadIdx.x; i < NX; i += NT) tw[i] = twx[i];
     fft_ld<NX, NPI, NT, +1, PS, 1, false, false, HermLoader<NX, ROWS>, NoSt, true>(s, tw, HermLoader<NX, ROWS>{D9, g, row0}, NoSt{});
@@ -430,24 +514,31 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
     float ep[VISC ? CPT : 1][9], vm[VISC ? CPT : 1][5];
     int jr[CPT][2];
     bool ok[CPT], in[CPT];
+    const int z0 = row0 / g.ny, y0 = row0 - z0 * g.ny;   // ROWS <= 16 <= ny: at most one step in z
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
         const int c = threadIdx.x + i * NT;
-        const int r = c / NX, x = c - r * NX;
-        const int row = row0 + r;
-        ok[i] = c < ROWS * NX && row < g.nrows;
-        const int rr = ok[i] ? row : row0;
-        const int y = rr % g.ny, z = rr / g.ny;
-        const long cell = (long)rr * NX + x;
+        const int r = wave_row<NX>(c / NX), x = c - r * NX;
+        ok[i] = c < ROWS * NX && row0 + r < g.nrows;
+        // lanes past the block's or the grid's rows follow the last row (their
+        // loads are valid, they store nothing), so a wave's rows never decrease
+        const int rr = min(min(r, ROWS - 1), g.nrows - 1 - row0);
+        const bool up = y0 + rr >= g.ny;
+        const int y = y0 + rr - (up ? g.ny : 0), z = z0 + (up ? 1 : 0);
+        const unsigned cell = 4u * ((unsigned)(row0 + rr) * NX + x);   // byte offset
         in[i] = undamped(pm, x, y, z);
         // an undamped cell reads only the first part of each component
 #pragma unroll
-        for (int q = 0; q < 15; ++q) sp[i][q] = first_part(q) || !in[i] ? F[(long)q * g.n + cell] : 0.f;
-        mt[i][0] = m.dlam[cell];
-        mt[i][1] = m.dmu2[cell];
-        mt[i][2] = m.dmus[0][cell];
-        mt[i][3] = m.dmus[1][cell];
-        mt[i][4] = m.dmus[2][cell];
+        for (int q = 0; q < 15; ++q) sp[i][q] = first_part(q) ? ldf(F + q * g.n, cell) : 0.f;
+        if (!in[i])
+#pragma unroll
+            for (int q = 0; q < 15; ++q)
+                if (!first_part(q)) sp[i][q] = ldf(F + q * g.n, cell);
+        mt[i][0] = ldf(m.dlam, cell);
+        mt[i][1] = ldf(m.dmu2, cell);
+        mt[i][2] = ldf(m.dmus[0], cell);
+        mt[i][3] = ldf(m.dmus[1], cell);
+        mt[i][4] = ldf(m.dmus[2], cell);
         const float bxi = pm.bi[0][x], bxh = pm.bh[0][x];
         const float byi = pm.bi[1][y], byh = pm.bh[1][y];
         const float bzi = pm.bi[2][z], bzh = pm.bh[2][z];
@@ -462,16 +553,16 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
         fa[i][6] = pm.ah[2][z] * bxh * byi;   // xz, z part
         fa[i][7] = pm.ah[1][y] * bxi * bzh;   // yz, y part
         fa[i][8] = pm.ah[2][z] * bxi * byh;   // yz, z part
-        jr[i][0] = iptr[rr];
-        jr[i][1] = iptr[rr + 1];
+        jr[i][0] = iptr[row0 + rr];
+        jr[i][1] = iptr[row0 + rr + 1];
         if constexpr (VISC) {
 #pragma unroll
-            for (int q = 0; q < 9; ++q) ep[i][q] = EP[(long)ep_slot(q) * g.n + cell];
-            vm[i][0] = m.chi[cell];
-            vm[i][1] = m.eta2[cell];
-            vm[i][2] = m.etas[0][cell];
-            vm[i][3] = m.etas[1][cell];
-            vm[i][4] = m.etas[2][cell];
+            for (int q = 0; q < 9; ++q) ep[i][q] = ldf(EP + ep_slot(q) * g.n, cell);
+            vm[i][0] = ldf(m.chi, cell);
+            vm[i][1] = ldf(m.eta2, cell);
+            vm[i][2] = ldf(m.etas[0], cell);
+            vm[i][3] = ldf(m.etas[1], cell);
+            vm[i][4] = ldf(m.etas[2], cell);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -480,12 +571,9 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
         const int c = threadIdx.x + i * NT;
-        const int r = c / NX, x = c - r * NX;
-        const int row = row0 + r;
-#pragma unroll
-        for (int q = 0; q < 6; ++q) ssum[i][q] = 0.f;
-        if (!ok[i]) continue;
-        const long cell = (long)row * NX + x;
+        const int r = wave_row<NX>(min(c / NX, ROWS - 1)), x = c - wave_row<NX>(c / NX) * NX;
+        const int idx = min(row0 + r, g.nrows - 1) * NX + x;
+        const unsigned cell = 4u * (unsigned)idx;
         const float dlam = mt[i][0], dmu2 = mt[i][1];
         const float mxy = mt[i][2], mxz = mt[i][3], myz = mt[i][4];
         const float ai[3] = {fa[i][0], fa[i][1], fa[i][2]};
@@ -531,19 +619,31 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
         sp[i][13] = ayz_y * (ayz_y * sp[i][13] + sh[4]);
         sp[i][14] = ayz_z * (ayz_z * sp[i][14] + sh[5]);
         if constexpr (VISC) {
+            if (ok[i])
 #pragma unroll
-            for (int q = 0; q < 9; ++q) EP[(long)ep_slot(q) * g.n + cell] = e[q];
+                for (int q = 0; q < 9; ++q) stf(EP + ep_slot(q) * g.n, cell, e[q]);
         }
-        // point sources of this shot in this row
-        const int j0 = jr[i][0], j1 = jr[i][1];
-        if (j0 != j1 && step < inj.nt_w) {
-            for (int j = j0; j < j1; ++j) {
-                const int4 q = inj.ent[j];
-                if (q.x != x) continue;
-                const float val = __int_as_float(q.z) * inj.wav[(long)q.w * inj.nt_w + step];
+        // point sources: the entries of the wave's rows, 64 at a time, one load
+        // per lane, then field by field through scalar registers.  (Read one by
+        // one by every thread, the entries of a smoothed source held their block
+        // 100 us after all others had ended, those of a point source 4.)
+        const int ja = __builtin_amdgcn_readfirstlane(jr[i][0]), jb = __builtin_amdgcn_readlane(jr[i][1], 63);
+        if (ja != jb && step < inj.nt_w) {
+            const int lane = threadIdx.x & 63;
+            for (int j = ja; j < jb; j += 64) {
+                int4 q = make_int4(0, -1, 0, 0);
+                float val = 0.f;
+                if (j + lane < jb) {
+                    q = inj.ent[j + lane];
+                    val = __int_as_float(q.z) * inj.wav[(long)q.w * inj.nt_w + step];
+                }
 #pragma unroll
                 for (int f = 0; f < 15; ++f)
-                    if (q.y == f) sp[i][f] += val;
+                    for (unsigned long long of = __ballot(q.y == f); of; of &= of - 1) {
+                        const int l = __builtin_ctzll(of);
+                        const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(val), l));
+                        sp[i][f] += idx == __builtin_amdgcn_readlane(q.x, l) ? v : 0.f;
+                    }
             }
         }
         ssum[i][0] = sp[i][0] + sp[i][1] + sp[i][2];
@@ -561,9 +661,15 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
             sp[i][11] = ssum[i][4];
             sp[i][13] = ssum[i][5];
         }
+        if (ok[i]) {
 #pragma unroll
-        for (int q = 0; q < 15; ++q)
-            if (first_part(q) || !in[i]) F[(long)q * g.n + cell] = sp[i][q];
+            for (int q = 0; q < 15; ++q)
+                if (first_part(q)) stf(F + q * g.n, cell, sp[i][q]);
+            if (!in[i])
+#pragma unroll
+                for (int q = 0; q < 15; ++q)
+                    if (!first_part(q)) stf(F + q * g.n, cell, sp[i][q]);
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -576,8 +682,6 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
     }
     __syncthreads();
     {
-        const int rend = min(row0 + ROWS, g.nrows);
-        const int e0 = rc.ptr[row0], e1 = rc.ptr[rend];
         const int tn = step - n0;
         for (int e = e0 + threadIdx.x; e < e1; e += NT) {
             const int4 q = rc.ent[e];
@@ -750,7 +854,6 @@ __global__ __launch_bounds__(NT) void k_yinv(Geo g, const float2* __restrict__ t
                                              const ZDesc* __restrict__ zd, int phase, int nsrc)
 {
     constexpr int IS = TX + 1;
-    constexpr int R0 = plan_radix(NY, 0), Q = (TX * (NY / R0) + NT - 1) / NT;
     // the y symbol goes to LDS where it fits beside the tile
     constexpr bool SYL = (long)NY * (IS + 2) * 8 <= 65536;
     static_assert(NT % TX == 0, "a thread keeps its column");

@@ -362,6 +362,37 @@ def test_blackman_smoothed_sources_against_oracle(B):
             assert e <= TOL
 
 
+@pytest.mark.parametrize("shape,smooth", [((30, 24, 20), 1), ((30, 75, 75), 1), ((20, 24, 128), 1), ((30, 75, 75), 0)])
+def test_injected_stress_of_many_sources(B, shape, smooth):
+    """Source injection where a wave's rows hold more entries than it has lanes
+    and several sources add to one cell: coinciding and neighbouring sources in
+    the second shot, one in the last row (whose stencil wraps), rows shorter
+    than a wave, of a length that leaves a ragged last block, and longer.  From
+    rest, one step leaves exactly the injected stress: up to 16 roundings of
+    2^-24 per value against the oracle's state."""
+    nz, ny, nx = shape
+    w = small_workload(shape=shape, nt=1, shots=2, seed=17)
+    w.smooth = smooth
+    c = [nx // 2, ny // 2, nz - 12]
+    w.src_ijk = np.array([c, c, [c[0] + 1, c[1], c[2]], [nx - 1, ny - 1, nz - 1]], np.int32)
+    w.wavelet = np.random.default_rng(18).standard_normal((4, 1))
+    s = B.Solver.from_workload(w)
+    s.set_workload_sources(w)
+    s.run(1)
+    for k in range(w.n_shots):
+        q = slice(w.shot_ofs[k], w.shot_ofs[k + 1])
+        o = oracle.Solver.from_workload(w)
+        o.set_sources(w.src_ijk[q], w.src_m[q], w.wavelet[q])
+        o.run(1)
+        got, ref = physics.summed(s.get_state(k).astype(np.float64)), physics.summed(o.get_state())
+        for f in range(3, 9):
+            e = rel(got[f], ref[f])
+            say(f"  {shape} smooth {smooth} shot {k} stress {f - 3} rel-L2 {e:.3e}")
+            assert e <= 16 * 2.0 ** -24
+        o.close()
+    s.close()
+
+
 # ---------------------------------------------------------------------------
 def viscous_workload(nt=150, shots=2, seed=21, kspace=1):
     """The small heterogeneous workload with Kelvin-Voigt viscosities: chi and
