@@ -134,10 +134,10 @@ int pstd3d_state_fields(const pstd3d_ctx *c);
  * PSTD_EUNSTABLE if a non-finite value reached the receivers. */
 int pstd3d_run(pstd3d_ctx *c, int nt, float *traces_dev, void *hip_stream);
 
-/* Advance several contexts (uneven grids allowed) by nt steps as one HIP
- * graph per step: the per-context step sequences are captured on forked
- * streams so the graph runs them concurrently; traces[i] is context i's
- * device trace buffer.  All contexts must live on the current device. */
+/* Advance several contexts (uneven grids allowed) by nt steps side by side:
+ * each context's steps replay a HIP graph on a stream of its own, from what is
+ * queued on `hip_stream` at the call on; traces[i] is context i's device trace
+ * buffer.  All contexts must live on the current device. */
 int pstd3d_run_many(pstd3d_ctx *const *ctxs, int n, int nt, float *const *traces, void *hip_stream);
 
 /* Checkpoint: copy shot `shot`'s state (float, host [F][nz][ny][nx] with

@@ -225,6 +225,10 @@ struct pstd3d_ctx {
     int* flag = nullptr;
     long step = 0;
     long bytes = 0;
+    // the context's own stream (its steps are captured on it, and run on it
+    // beside other contexts' in pstd3d_run_many), and an event to start such runs by
+    hipStream_t own_st = nullptr;
+    hipEvent_t own_ev = nullptr;
     // per-kernel event timing
     bool prof = false;
     std::vector<hipEvent_t> evpool;
@@ -238,6 +242,8 @@ struct pstd3d_ctx {
         release_shots();
         release_model();
         for (auto e : evpool) (void)hipEventDestroy(e);
+        if (own_ev) (void)hipEventDestroy(own_ev);
+        if (own_st) (void)hipStreamDestroy(own_st);
     }
 
     // record a start event for `kind`; returns the pool index (or -1)
@@ -1011,61 +1017,21 @@ static int check_traces(pstd3d_ctx* c, const float* traces, long count, hipStrea
     return PSTD_OK;
 }
 
-// HIP graph of two consecutive steps of several contexts: each context's two
-// steps are captured on its own stream branch (forked from and joined into a
-// private origin stream), so independent models run concurrently.
-static int capture_pair(pstd3d_ctx* const* ctxs, int n, float* const* traces, const int* n0, int ldt,
-                        hipGraphExec_t* out)
+// HIP graph of two consecutive steps of a context, captured on its own stream
+static int capture_pair(pstd3d_ctx* c, float* traces, int n0, int ldt, hipGraphExec_t* out)
 {
-    hipStream_t origin = nullptr;
-    std::vector<hipStream_t> br(n, nullptr);
-    std::vector<hipEvent_t> join(n, nullptr);
-    hipEvent_t fork = nullptr;
+    if (!c->own_st) HIP_TRY(hipStreamCreateWithFlags(&c->own_st, hipStreamNonBlocking));
+    if (!c->own_ev) HIP_TRY(hipEventCreateWithFlags(&c->own_ev, hipEventDisableTiming));
     hipGraph_t graph = nullptr;
-    int rc = PSTD_OK;
-    auto cleanup = [&]() {
-        if (graph) (void)hipGraphDestroy(graph);
-        for (auto e : join)
-            if (e) (void)hipEventDestroy(e);
-        if (fork) (void)hipEventDestroy(fork);
-        for (auto s : br)
-            if (s) (void)hipStreamDestroy(s);
-        if (origin) (void)hipStreamDestroy(origin);
-    };
-#define CAP_TRY(expr)                                                                    \
-    do {                                                                                 \
-        hipError_t e_ = (expr);                                                          \
-        if (e_ != hipSuccess) {                                                          \
-            rc = fail(PSTD_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_));  \
-            cleanup();                                                                   \
-            return rc;                                                                   \
-        }                                                                                \
-    } while (0)
-    CAP_TRY(hipStreamCreateWithFlags(&origin, hipStreamNonBlocking));
-    CAP_TRY(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
-    for (int i = 0; i < n; ++i) {
-        CAP_TRY(hipStreamCreateWithFlags(&br[i], hipStreamNonBlocking));
-        CAP_TRY(hipEventCreateWithFlags(&join[i], hipEventDisableTiming));
-    }
-    CAP_TRY(hipStreamBeginCapture(origin, hipStreamCaptureModeThreadLocal));
-    hipError_t ce = hipEventRecord(fork, origin);
-    for (int i = 0; i < n && ce == hipSuccess; ++i) {
-        ce = hipStreamWaitEvent(br[i], fork, 0);
-        for (int s = 0; s < 2 && ce == hipSuccess; ++s) enqueue_step(ctxs[i], br[i], traces[i], n0[i], ldt, (n0[i] + s) & 1);
-        if (ce == hipSuccess) ce = hipGetLastError();
-        if (ce == hipSuccess) ce = hipEventRecord(join[i], br[i]);
-        if (ce == hipSuccess) ce = hipStreamWaitEvent(origin, join[i], 0);
-    }
-    hipError_t ee = hipStreamEndCapture(origin, &graph);
-    if (ce != hipSuccess || ee != hipSuccess) {
-        rc = fail(PSTD_EDEVICE, std::string("graph capture: ") + hipGetErrorString(ce != hipSuccess ? ce : ee));
-        cleanup();
-        return rc;
-    }
-    CAP_TRY(hipGraphInstantiate(out, graph, nullptr, nullptr, 0));
-    cleanup();
+    HIP_TRY(hipStreamBeginCapture(c->own_st, hipStreamCaptureModeThreadLocal));
+    for (int s = 0; s < 2; ++s) enqueue_step(c, c->own_st, traces, n0, ldt, (n0 + s) & 1);
+    hipError_t e = hipGetLastError();
+    const hipError_t ee = hipStreamEndCapture(c->own_st, &graph);
+    if (e == hipSuccess) e = ee;
+    if (e == hipSuccess) e = hipGraphInstantiate(out, graph, nullptr, nullptr, 0);
+    if (graph) (void)hipGraphDestroy(graph);
+    if (e != hipSuccess) return fail(PSTD_EDEVICE, std::string("graph capture: ") + hipGetErrorString(e));
     return PSTD_OK;
-#undef CAP_TRY
 }
 
 static bool graphs_enabled()
@@ -1074,8 +1040,13 @@ static bool graphs_enabled()
     return !(e && e[0] == '0');
 }
 
-// Advance contexts by nt steps: pairs of steps replay one captured graph,
-// an odd last step (and runs with event timing) go out eagerly.
+// Advance contexts by nt steps: pairs of steps replay a captured graph per
+// context, an odd last step (and runs with event timing) go out eagerly.
+// Several contexts run side by side, each on its own stream from an event of
+// `st` on (the host waits for all of them): a context goes on to its next steps
+// without waiting for the others.  (As branches of one graph all waited for the
+// largest model after every pair of steps, and the process was seen to end
+// with a segmentation fault now and then in runs over many branches.)
 static int advance(pstd3d_ctx* const* ctxs, int n, int nt, float* const* traces, hipStream_t st)
 {
     std::vector<int> n0(n);
@@ -1086,18 +1057,27 @@ static int advance(pstd3d_ctx* const* ctxs, int n, int nt, float* const* traces,
     }
     int done = 0;
     if (!prof && graphs_enabled() && nt >= 4) {
-        hipGraphExec_t ex = nullptr;
-        int rc = capture_pair(ctxs, n, traces, n0.data(), nt, &ex);
-        if (rc) return rc;
-        for (; done + 2 <= nt; done += 2) {
-            hipError_t e = hipGraphLaunch(ex, st);
-            if (e != hipSuccess) {
-                (void)hipGraphExecDestroy(ex);
-                return fail(PSTD_EDEVICE, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
+        std::vector<hipGraphExec_t> ex(n, nullptr);
+        int rc = PSTD_OK;
+        for (int i = 0; i < n && rc == PSTD_OK; ++i) rc = capture_pair(ctxs[i], traces[i], n0[i], nt, &ex[i]);
+        hipError_t e = hipSuccess;
+        if (rc == PSTD_OK && n > 1) {
+            e = hipEventRecord(ctxs[0]->own_ev, st);
+            for (int i = 0; i < n && e == hipSuccess; ++i) e = hipStreamWaitEvent(ctxs[i]->own_st, ctxs[0]->own_ev, 0);
+        }
+        if (rc == PSTD_OK) {
+            for (; done + 2 <= nt && e == hipSuccess; done += 2)
+                for (int i = 0; i < n && e == hipSuccess; ++i) e = hipGraphLaunch(ex[i], n > 1 ? ctxs[i]->own_st : st);
+            // everything launched ends before its graph (and, after an error, the caller's buffers) can go
+            for (int i = 0; i < n; ++i) {
+                const hipError_t se = hipStreamSynchronize(n > 1 ? ctxs[i]->own_st : st);
+                if (e == hipSuccess) e = se;
             }
         }
-        HIP_TRY(hipStreamSynchronize(st));
-        (void)hipGraphExecDestroy(ex);
+        for (auto x : ex)
+            if (x) (void)hipGraphExecDestroy(x);
+        if (rc != PSTD_OK) return rc;
+        if (e != hipSuccess) return fail(PSTD_EDEVICE, std::string("graph launch: ") + hipGetErrorString(e));
     }
     for (; done < nt; ++done) {
         for (int i = 0; i < n; ++i) {
