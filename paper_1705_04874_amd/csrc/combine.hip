@@ -12,7 +12,7 @@
 // record is written once.
 //
 // Two kernels share that scheme.  When a whole input trace fits a slot of the
-// staging buffer (nt_in + 4 values, two zeros on each side; up to 4 CT),
+// staging buffer (nt_in + 4 values, two zeros on each side; up to 16 CT),
 // k_combine_w stages the rows of several sources between one pair of
 // barriers and clamps each sample's index into its slot (an index outside
 // the trace lands on the two zero pads at either end, so no sample needs a
@@ -21,7 +21,8 @@
 // windows of samples it touches, so a wave spends lanes only where an event
 // is.  Longer traces go through k_combine, whose threads own SPT consecutive
 // samples and which stages one source at a time in chunks of STG samples and
-// tests every sample against the chunk.  Blocks of 512 threads (segments of
+// tests every sample against the chunk (16 x 1024 x 4 traces of 4000 samples
+// into 100 events of 12000: 930 us, and 408 us by whole traces).  Blocks of 512 threads (segments of
 // 6144 samples) measured faster than 1024: fewer waves wait at each item's
 // barriers for the busiest one.
 //
@@ -40,6 +41,7 @@
 #include <cmath>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "pstd3d.h"
@@ -85,6 +87,17 @@ struct EvC {
     int lo, hi;
     int pad;
 };
+// and for traces of more than 4 CT - 4 samples, whose amplitudes follow in an
+// array of their own: four components take no more of a bounded work-list
+// memory than the one Ev that is counted for them
+struct EvL {
+    unsigned long long u0;
+    unsigned win;
+    int pad;
+};
+static_assert(4 * sizeof(EvL) + sizeof(double) <= sizeof(Ev), "the plan's bytes hold both");
+// the longest traces staged whole with each record
+constexpr int NT_IN_C = 4 * CT - 4, NT_IN_L = 16 * CT - 4;
 
 // x in 32.32 fixed point modulo 2^64 (two's complement): the integer part in
 // the high word, the fraction truncated to 32 bits in the low word.  |x| is
@@ -105,7 +118,9 @@ struct Plan {
     std::vector<int> seg_ptr;    // [nseg + 1] into grp
     std::vector<Grp> grp;
     std::vector<Ev> ev;
-    std::vector<EvC> evc;        // [4][ev.size()]
+    std::vector<EvC> evc;        // [4][ev.size()], nt_in <= NT_IN_C
+    std::vector<EvL> evl;        // [4][ev.size()], nt_in <= NT_IN_L, and
+    std::vector<double> amp;     // behind them the amplitudes
     size_t off_ptr = 0, off_grp = 0, off_ev = 0, bytes = 0;
 };
 
@@ -190,7 +205,9 @@ void make_plan(Plan& p, int n_rec, int n_ev, const int32_t* src_idx, const doubl
     // kernel the per-event ones
     const size_t n = p.ev.size();
     p.evc.clear();
-    if (nt_in + 4 <= 4 * CT) {
+    p.evl.clear();
+    p.amp.clear();
+    if (nt_in <= NT_IN_C) {
         p.evc.resize(4 * n);
         for (int c = 0; c < 4; ++c)
             for (size_t i = 0; i < n; ++i) {
@@ -199,6 +216,15 @@ void make_plan(Plan& p, int n_rec, int n_ev, const int32_t* src_idx, const doubl
             }
         p.bytes = p.off_ev + align256(std::max<size_t>(1, p.evc.size()) * sizeof(EvC));
     } else {
+        if (nt_in <= NT_IN_L) {
+            p.evl.resize(4 * n);
+            for (int c = 0; c < 4; ++c)
+                for (size_t i = 0; i < n; ++i) {
+                    const Ev& E = p.ev[i];
+                    p.evl[c * n + i] = EvL{E.u0[c], E.win[c], 0};
+                }
+            for (const Ev& E : p.ev) p.amp.push_back(E.amp);
+        }
         p.bytes = p.off_ev + align256(std::max<size_t>(1, n) * sizeof(Ev));
     }
 }
@@ -334,7 +360,7 @@ __global__ __launch_bounds__(CT) __attribute__((amdgpu_waves_per_eu(8))) void k_
 
 // Whole-trace staging: a slot holds a source row x[-2 .. nt_in + 1] (zeros
 // outside the trace), nt_in + 4 values, in VPS CT floats of which each thread
-// writes VPS (VPS = 1, 2 or 4: the smallest with nt_in + 4 <= VPS CT); an item
+// writes VPS (a power of two up to 16: the smallest with nt_in + 4 <= VPS CT); an item
 // is NSLOT(VPS) = WPT / VPS slots, staged from WPT registers per thread
 // (32 KB of LDS).  The loads are buffer loads whose range is the trace, so
 // the positions outside it read zero and staging needs no branch, clamp or
@@ -358,7 +384,7 @@ struct GroupPos {
 
 __host__ __device__ constexpr int w_slot(int nt_in) { return nt_in + 4; }
 
-template <int VPS>
+template <int VPS, class Rec>
 __global__ __launch_bounds__(CT) __attribute__((amdgpu_waves_per_eu(8))) void k_combine_w(
     const float* __restrict__ tr, int nseg, int n_rec, int nt_in, double ratio, unsigned long long ratio_fx,
     GroupPos gp, const char* __restrict__ plan, long off_grp, long off_ev, int n_evp, int seg_len, int nt_out,
@@ -377,7 +403,10 @@ __global__ __launch_bounds__(CT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     const int wsh = (__builtin_amdgcn_readfirstlane(tid) / 64) * NGRP;
     const int* __restrict__ seg_ptr = reinterpret_cast<const int*>(plan);
     const Grp* __restrict__ grp = reinterpret_cast<const Grp*>(plan + off_grp);
-    const EvC* __restrict__ ev = reinterpret_cast<const EvC*>(plan + off_ev) + (long)c * n_evp;
+    constexpr bool LONG = std::is_same_v<Rec, EvL>;
+    const Rec* __restrict__ ev = reinterpret_cast<const Rec*>(plan + off_ev) + (long)c * n_evp;
+    const double* __restrict__ amps =
+        reinterpret_cast<const double*>(plan + off_ev + 4L * n_evp * (long)sizeof(Rec));   // LONG only
     // this block's row (c, r) of source 0; a group adds its source's offset
     const float* __restrict__ rowp = tr + ((long)c * n_rec + r) * nt_in;
     double acc[SPT];
@@ -393,14 +422,19 @@ __global__ __launch_bounds__(CT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     // trace as the buffer's range return zero outside it (a negative offset
     // is out of range as an unsigned value)
     float pre[WPT];
-    // byte offsets of x[tid - 2] and x[tid + 2 CT - 2]; the other loads add
-    // constants that fit the instructions' offset field
-    const int o0 = (tid - 2) * 4, o2 = o0 + 2 * CT * 4;
+    // byte offsets of x[tid - 2 + 2 i CT]; the loads between add constants that
+    // fit the instructions' offset field
+    constexpr int NB = (VPS + 1) / 2;
+    const int o0 = (tid - 2) * 4;
     auto fetch = [&](int item) {
         // opaque copies, so the per-load constants stay in the loads'
         // offset fields rather than in registers set up outside the loop
-        int b0 = o0, b2 = o2;
-        asm volatile("" : "+v"(b0), "+v"(b2));
+        int b[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            b[i] = o0 + i * 2 * CT * 4;
+            asm volatile("" : "+v"(b[i]));
+        }
         const int gb = g0 + item * NSLOT;
 #pragma unroll
         for (int sl = 0; sl < NSLOT; ++sl) {
@@ -412,7 +446,7 @@ __global__ __launch_bounds__(CT) __attribute__((amdgpu_waves_per_eu(8))) void k_
 #pragma unroll
             for (int v = 0; v < VPS; ++v)
                 pre[sl * VPS + v] = __uint_as_float(
-                    __builtin_amdgcn_raw_buffer_load_b32(rs, (v < 2 ? b0 : b2) + (v & 1) * CT * 4, 0, 0));
+                    __builtin_amdgcn_raw_buffer_load_b32(rs, b[v / 2] + (v & 1) * CT * 4, 0, 0));
         }
     };
     if (nitems > 0) fetch(0);
@@ -430,14 +464,16 @@ __global__ __launch_bounds__(CT) __attribute__((amdgpu_waves_per_eu(8))) void k_
             const Grp G = grp[gb + gi];
             const float* __restrict__ x = stw + gi * S;
             for (int e = G.e0; e < G.e1; ++e) {
-                const EvC E = ev[e];
+                const Rec E = ev[e];
+                double amp;
+                if constexpr (LONG) amp = amps[e];
+                else amp = E.amp;
                 // one round trip for the whole record: make its fields live
                 // before the test below uses the mask
-                asm volatile("" ::"s"(E.u0), "s"(E.amp), "s"(E.win));
+                asm volatile("" ::"s"(E.u0), "s"(amp), "s"(E.win));
                 // this wave's windows that the event touches
                 const unsigned wm = (E.win >> wsh) & ((1u << NGRP) - 1);
                 if (!wm) continue;
-                const double amp = E.amp;
                 const unsigned long long ue = T + E.u0;
 #pragma unroll
                 for (int j = 0; j < NGRP; ++j) {
@@ -529,6 +565,11 @@ int launch(const Plan& p, char* dplan, const float* tr, int n_rec, int nt_in, do
     if (ok && !p.evc.empty())
         ok = hipMemcpyAsync(dplan + p.off_ev, p.evc.data(), p.evc.size() * sizeof(EvC), hipMemcpyHostToDevice, st) ==
              hipSuccess;
+    else if (ok && !p.evl.empty())
+        ok = hipMemcpyAsync(dplan + p.off_ev, p.evl.data(), p.evl.size() * sizeof(EvL), hipMemcpyHostToDevice, st) ==
+                 hipSuccess &&
+             hipMemcpyAsync(dplan + p.off_ev + p.evl.size() * sizeof(EvL), p.amp.data(), p.amp.size() * sizeof(double),
+                            hipMemcpyHostToDevice, st) == hipSuccess;
     else if (ok && !p.ev.empty())
         ok = hipMemcpyAsync(dplan + p.off_ev, p.ev.data(), p.ev.size() * sizeof(Ev), hipMemcpyHostToDevice, st) ==
              hipSuccess;
@@ -542,15 +583,20 @@ int launch(const Plan& p, char* dplan, const float* tr, int n_rec, int nt_in, do
         const int nev = (int)p.ev.size();
         GroupPos gp;
         for (int j = 0; j < NGRP; ++j) gp.d[j] = to_fx((double)j * GSPAN * ratio + 2.0);
+        auto whole = [&](auto fn) {
+            hipLaunchKernelGGL(fn, grid, dim3(CT), (size_t)WPT * CT * sizeof(float), st, tr, p.nseg, n_rec, nt_in,
+                               ratio, rfx, gp, dplan, og, oe, nev, p.seg_len, nt_out, out);
+        };
         if (L <= CT) {
-            hipLaunchKernelGGL(k_combine_w<1>, grid, dim3(CT), (size_t)WPT * CT * sizeof(float), st, tr, p.nseg,
-                               n_rec, nt_in, ratio, rfx, gp, dplan, og, oe, nev, p.seg_len, nt_out, out);
+            whole(k_combine_w<1, EvC>);
         } else if (L <= 2 * CT) {
-            hipLaunchKernelGGL(k_combine_w<2>, grid, dim3(CT), (size_t)WPT * CT * sizeof(float), st, tr, p.nseg,
-                               n_rec, nt_in, ratio, rfx, gp, dplan, og, oe, nev, p.seg_len, nt_out, out);
+            whole(k_combine_w<2, EvC>);
         } else if (L <= 4 * CT) {
-            hipLaunchKernelGGL(k_combine_w<4>, grid, dim3(CT), (size_t)WPT * CT * sizeof(float), st, tr, p.nseg,
-                               n_rec, nt_in, ratio, rfx, gp, dplan, og, oe, nev, p.seg_len, nt_out, out);
+            whole(k_combine_w<4, EvC>);
+        } else if (L <= 8 * CT) {
+            whole(k_combine_w<8, EvL>);
+        } else if (L <= 16 * CT) {
+            whole(k_combine_w<16, EvL>);
         } else {
             hipLaunchKernelGGL(k_combine, dim3(row_blocks(p.nseg, n_rec)), dim3(CT), 0, st, tr, p.nseg, n_rec, nt_in,
                                ratio, ratio_fx,

@@ -156,6 +156,27 @@ def test_staging_slot_boundaries(B, nt_in):
     check(got, ref)
 
 
+@pytest.mark.parametrize("nt_in", [2045, 4092, 4093, 8188, 8189])
+def test_long_traces_around_the_staging_slots(B, nt_in):
+    """Traces that fill eight and sixteen staged values per thread exactly, and
+    one past each (the next slot shape, then the chunked staging); events
+    overlap both trace ends, one source has none and one has most of them."""
+    import torch
+    rng = np.random.default_rng(nt_in)
+    n_src, n_rec = 5, 3
+    tr = rng.standard_normal((n_src, 4, n_rec, nt_in)).astype(np.float32)
+    t0 = [1e-3, 0.5e-3, 0.5e-3, 0.5e-3]
+    n_ev = 40
+    src = np.where(rng.random(n_ev) < 0.6, 3, rng.integers(0, 4, n_ev)).astype(np.int32)
+    amp = rng.lognormal(0, 1, n_ev)
+    to = rng.uniform(-1.2 * nt_in * 1e-3, 1.2 * nt_in * 1e-3, n_ev)
+    nt_out, dt_out = nt_in + 4099, 0.9e-3
+    say("combine long traces", nt_in)
+    got = B.seis_combine(torch.from_numpy(tr).cuda(), t0, src, amp, to, nt_out, 1e-3, dt_out).cpu().numpy()
+    ref = oracle.combine(tr, t0, src, amp, to, nt_out, 1e-3, dt_out)
+    check(got, ref)
+
+
 @pytest.mark.parametrize("nt_in,nt_out,ratio", [
     (300, 1, 1.0), (300, 255, 1.0), (300, 257, 0.37), (1500, 2049, 1.0), (1500, 6144, 1.3),
     (1500, 6145, 1.3), (300, 12289, 7.3), (1500, 3000, 0.05)])
