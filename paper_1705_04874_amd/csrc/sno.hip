@@ -57,6 +57,20 @@ __device__ __forceinline__ short to_bf16(float f)
     return (short)(u >> 16);
 }
 
+int grid_for(long n) { return (int)std::min<long>((n + 255) / 256, 4096); }
+
+__global__ void k_gelu(const float* __restrict__ z, float* __restrict__ y, long n)
+{
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
+        y[i] = gelu_f(z[i]);
+}
+
+__global__ void k_gelu_bwd(const float* __restrict__ dy, const float* __restrict__ z, float* __restrict__ dz, long n)
+{
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
+        dz[i] = dy[i] * gelu_d(z[i]);
+}
+
 struct GemmP {
     int M, N, K, KB;
     const float* A;
@@ -70,7 +84,16 @@ struct GemmP {
     long sBiasb;
     int nsplit;          // > 1: blockIdx.z splits the (kb, k) slices of one product (batch 1);
     float* part;         // split z writes its partial sum to part + z M N (row-major)
+    int epi;             // EPI_*, with E laid out like C
+    float* E;
+    bool wide;           // rows of C are whole, aligned float4
 };
+// what a product's epilogue does with the values v it has formed
+// (16 samples, 1024 hidden rows: 60 and 108 us as a product and a pass, 43 and
+// 82 in one)
+constexpr int EPI_NONE = 0;
+constexpr int EPI_GELU = 1;      // C = v, E = gelu(v)
+constexpr int EPI_GELU_BWD = 2;  // C = v gelu'(E)
 
 __global__ __launch_bounds__(256) void k_gemm(GemmP p)
 {
@@ -139,15 +162,20 @@ __global__ __launch_bounds__(256) void k_gemm(GemmP p)
 // Every float4 the kernel loads is either wholly inside or wholly outside the
 // operand (the contiguous extent is a multiple of 4 and the other strides are
 // multiples of 4), so the out-of-range ones are zeros.
-constexpr int GK = 32;          // k per slice
-constexpr int GLD = GK + 8;     // LDS row length in BF16 (80 bytes: conflict-free 16-byte reads)
+constexpr int GK = 32;   // k per slice (LDS rows have 8 BF16 more: conflict-free 16-byte reads)
 
-// One operand's slice: rows [r0, r0 + R) of the m (or n) axis, k [k0, k0 + 32).
+// Chunks of 8 k (16 bytes) of row r lie at chunk ^ (r / 16 mod 4) of their slice:
+// a row-contiguous operand's stores go to rows 4 apart, four bank groups without
+// it and sixteen with it; the reads (16 rows, one chunk) stay free of conflicts.
+__device__ __forceinline__ int swz(int row, int k) { return k ^ ((row >> 4 & 3) << 3); }
+
+// One operand's stage of KD slices: rows [r0, r0 + R) of the m (or n) axis, k [k0, k0 + 32 KD).
 // Sub-block sb of 4 rows x 4 k is loaded as 4 float4 and stored as 4 rows of
 // 4 BF16 (8 bytes each) into S[row][k].
-template <int R, bool KC>
+template <int R, bool KC, int KD = 1>
 struct Slice {
-    static constexpr int NSB = R * GK / 16;          // sub-blocks
+    static constexpr int W = GK * KD;                // k per stage
+    static constexpr int NSB = R * W / 16;           // sub-blocks
     static constexpr int PER = (NSB + 255) / 256;    // per thread
     float4 v[PER][4];
     __device__ __forceinline__ void load(const float* __restrict__ X, long sR, long sK, int nR, int nK, int r0, int k0)
@@ -156,10 +184,10 @@ struct Slice {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int sb = t + q * 256;
-            // k-contiguous: 8 neighbouring threads cover one row's 32 k;
+            // k-contiguous: 8 KD neighbouring threads cover one row's 32 KD k;
             // row-contiguous: R / 4 neighbouring threads cover one k's R rows
-            const int rb = KC ? sb / (GK / 4) : sb % (R / 4);
-            const int kb = KC ? sb % (GK / 4) : sb / (R / 4);
+            const int rb = KC ? sb / (W / 4) : sb % (R / 4);
+            const int kb = KC ? sb % (W / 4) : sb / (R / 4);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int r = r0 + rb * 4 + (KC ? i : 0), k = k0 + kb * 4 + (KC ? 0 : i);
@@ -169,15 +197,15 @@ struct Slice {
             }
         }
     }
-    __device__ __forceinline__ void store(__bf16 (*S)[GLD]) const
+    __device__ __forceinline__ void store(__bf16 (*S)[W + 8]) const
     {
         const int t = threadIdx.x;
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int sb = t + q * 256;
             if (NSB % 256 != 0 && sb >= NSB) continue;
-            const int rb = KC ? sb / (GK / 4) : sb % (R / 4);
-            const int kb = KC ? sb % (GK / 4) : sb / (R / 4);
+            const int rb = KC ? sb / (W / 4) : sb % (R / 4);
+            const int kb = KC ? sb % (W / 4) : sb / (R / 4);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 // row rb * 4 + i, k kb * 4 .. kb * 4 + 3
@@ -193,20 +221,38 @@ struct Slice {
                 }
                 typedef __bf16 bf4v __attribute__((ext_vector_type(4)));
                 bf4v w = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
-                *reinterpret_cast<bf4v*>(&S[rb * 4 + i][kb * 4]) = w;
+                *reinterpret_cast<bf4v*>(&S[rb * 4 + i][swz(rb * 4 + i, kb * 4)]) = w;
             }
         }
     }
 };
 
-template <int BM, int BN, bool AK, bool BK>
+// Consecutive blocks go to the chip's 8 XCDs in turn, each with an L2 of its
+// own: block L of n does work item xcd_item(L, n), so that an XCD takes a
+// contiguous run of items (tiles fastest, then the batch entry or split) and
+// its L2 holds the operands of the few entries it is at.  16 products of
+// 512 x 1024 x 1024: 55 us with items in block order, 43 so (bound by the L2's
+// loads of FP32 operands).
+__device__ __forceinline__ int xcd_item(int L, int n)
+{
+    const int x = L & 7, q = n >> 3, r = n & 7;
+    return x * q + min(x, r) + (L >> 3);
+}
+
+// KD: slices staged between two barriers (over 1: one kb, no split).  The
+// matrix instruction gets B as its rows, so a lane ends up with four
+// neighbouring columns of C and moves them by 16 bytes.  EPI: see EPI_*.
+template <int BM, int BN, bool AK, bool BK, int KD = 1, int EPI = EPI_NONE>
 __global__ __launch_bounds__(256) void k_gemm_t(GemmP p)
 {
     constexpr int TM = BM / 32, TN = BN / 32;     // 16 x 16 tiles per wave (2 x 2 waves)
+    constexpr int GLD = GK * KD + 8;
     __shared__ __attribute__((aligned(16))) __bf16 As[BM][GLD];
     __shared__ __attribute__((aligned(16))) __bf16 Bs[BN][GLD];
-    const int b = blockIdx.z;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+    const int nn = (p.N + BN - 1) / BN, tiles = nn * ((p.M + BM - 1) / BM);
+    const int item = xcd_item(blockIdx.x, gridDim.x);
+    const int b = item / tiles, tile = item - b * tiles;
+    const int m0 = tile / nn * BM, n0 = tile % nn * BN;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wm = (w >> 1) * (BM / 2), wn = (w & 1) * (BN / 2);
     f4 acc[TM][TN];
@@ -214,8 +260,8 @@ __global__ __launch_bounds__(256) void k_gemm_t(GemmP p)
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-    Slice<BM, AK> sa;
-    Slice<BN, BK> sb;
+    Slice<BM, AK, KD> sa;
+    Slice<BN, BK, KD> sb;
     const int nks = (p.K + GK - 1) / GK;
     // slices (kb, k0) of this block: all of them, or with a split its share
     int s_lo = 0, s_hi = p.KB * nks;
@@ -233,50 +279,97 @@ __global__ __launch_bounds__(256) void k_gemm_t(GemmP p)
         sb.load(p.B + ab * p.sBb + kb * p.sBkb, p.sBn, p.sBk, p.N, p.K, n0, k0);
     };
     if (s_lo < s_hi) load(s_lo);
-    for (int s = s_lo; s < s_hi; ++s) {
+    for (int s = s_lo; s < s_hi; s += KD) {
         sa.store(As);
         sb.store(Bs);
         __syncthreads();
-        if (s + 1 < s_hi) load(s + 1);
-        bf8 av[TM], bv[TN];
+        if (s + KD < s_hi) load(s + KD);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) av[i] = *reinterpret_cast<const bf8*>(&As[wm + i * 16 + (lane & 15)][8 * (lane >> 4)]);
+        for (int d = 0; d < KD; ++d) {
+            bf8 av[TM], bv[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bv[j] = *reinterpret_cast<const bf8*>(&Bs[wn + j * 16 + (lane & 15)][8 * (lane >> 4)]);
+            for (int i = 0; i < TM; ++i)
+                av[i] = *reinterpret_cast<const bf8*>(
+                    &As[wm + i * 16 + (lane & 15)][swz(wm + i * 16, d * GK + 8 * (lane >> 4))]);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+            for (int j = 0; j < TN; ++j)
+                bv[j] = *reinterpret_cast<const bf8*>(
+                    &Bs[wn + j * 16 + (lane & 15)][swz(wn + j * 16, d * GK + 8 * (lane >> 4))]);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[j], av[i], acc[i][j], 0, 0, 0);
+        }
         __syncthreads();
     }
+    const int mr = m0 + wm + (lane & 15), nc = n0 + wn + 4 * (lane >> 4);   // row, and first of four columns
     if (split) {
+        // (N is a multiple of 4 where B's columns are contiguous; else it may end inside the four)
         float* __restrict__ P = p.part + (long)b * p.M * p.N;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int row = m0 + wm + i * 16 + 4 * (lane >> 4) + q;
-                    const int col = n0 + wn + j * 16 + (lane & 15);
-                    if (row < p.M && col < p.N) P[(long)row * p.N + col] = acc[i][j][q];
-                }
+                for (int q = 0; q < 4; ++q)
+                    if (mr + i * 16 < p.M && nc + j * 16 + q < p.N)
+                        P[(long)(mr + i * 16) * p.N + nc + j * 16 + q] = acc[i][j][q];
         return;
     }
     float* __restrict__ C = p.C + b * p.sCb;
+    const float* __restrict__ bias = p.bias ? p.bias + b * p.sBiasb : nullptr;
+    if (p.wide) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = mr + i * 16;
+            if (row >= p.M) continue;
+            const float bs = bias ? bias[row] : 0.f;
+            float4 e[TN];
+            if constexpr (EPI == EPI_GELU_BWD)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    if (nc + j * 16 < p.N)
+                        e[j] = *reinterpret_cast<const float4*>(p.E + b * p.sCb + (long)row * p.sCm + nc + j * 16);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if (nc + j * 16 >= p.N) continue;
+                const long at = (long)row * p.sCm + nc + j * 16;
+                float4* c = reinterpret_cast<float4*>(C + at);
+                float v[4], o[4] = {0.f, 0.f, 0.f, 0.f};
+                if (p.beta != 0.f) *reinterpret_cast<float4*>(o) = *c;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    v[q] = p.alpha * acc[i][j][q];
+                    if (p.beta != 0.f) v[q] += p.beta * o[q];
+                    if (bias) v[q] += bs;
+                }
+                if constexpr (EPI == EPI_GELU)
+                    *reinterpret_cast<float4*>(p.E + b * p.sCb + at) =
+                        make_float4(gelu_f(v[0]), gelu_f(v[1]), gelu_f(v[2]), gelu_f(v[3]));
+                if constexpr (EPI == EPI_GELU_BWD) {
+                    v[0] *= gelu_d(e[j].x);
+                    v[1] *= gelu_d(e[j].y);
+                    v[2] *= gelu_d(e[j].z);
+                    v[3] *= gelu_d(e[j].w);
+                }
+                *c = make_float4(v[0], v[1], v[2], v[3]);
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int row = m0 + wm + i * 16 + 4 * (lane >> 4) + q;
-                const int col = n0 + wn + j * 16 + (lane & 15);
+                const int row = mr + i * 16, col = nc + j * 16 + q;
                 if (row < p.M && col < p.N) {
                     float* c = C + (long)row * p.sCm + (long)col * p.sCn;
                     float v = p.alpha * acc[i][j][q];
                     if (p.beta != 0.f) v += p.beta * (*c);
-                    if (p.bias) v += p.bias[b * p.sBiasb + row];
+                    if (bias) v += bias[row];
                     *c = v;
                 }
             }
@@ -316,14 +409,47 @@ bool tiled_ok(const float* X, long sR, long sK, long sB, long sKB, int nR, int n
     return false;
 }
 
+// the products that have an epilogue: the hidden map (EPI_GELU) and the
+// gradient to it (EPI_GELU_BWD)
+bool epi_built(const GemmP& p, bool ak, bool bk)
+{
+    return p.wide && ((p.epi == EPI_GELU && ak && !bk) || (p.epi == EPI_GELU_BWD && !ak && !bk));
+}
+
 template <int BM, int BN>
 void launch_tiled(hipStream_t st, const GemmP& p, int batch, bool ak, bool bk)
 {
-    const dim3 grid((p.N + BN - 1) / BN, (p.M + BM - 1) / BM, batch);
+    const dim3 grid((unsigned)(((p.N + BN - 1) / BN) * ((p.M + BM - 1) / BM) * batch));
+    if (p.epi != EPI_NONE && epi_built(p, ak, bk)) {
+        if (p.epi == EPI_GELU)
+            hipLaunchKernelGGL((k_gemm_t<BM, BN, true, false, 1, EPI_GELU>), grid, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((k_gemm_t<BM, BN, false, false, 1, EPI_GELU_BWD>), grid, dim3(256), 0, st, p);
+        return;
+    }
+    if constexpr (BM == 64 && BN == 64) {
+        // small tiles wait for memory once per stage: two slices a stage where
+        // the whole of k is pairs of slices
+        if (p.KB == 1 && p.nsplit == 1 && p.K % (2 * GK) == 0 && !ak && !bk) {
+            hipLaunchKernelGGL((k_gemm_t<64, 64, false, false, 2>), grid, dim3(256), 0, st, p);
+            return;
+        }
+    }
     if (ak && bk) hipLaunchKernelGGL((k_gemm_t<BM, BN, true, true>), grid, dim3(256), 0, st, p);
     else if (ak) hipLaunchKernelGGL((k_gemm_t<BM, BN, true, false>), grid, dim3(256), 0, st, p);
     else if (bk) hipLaunchKernelGGL((k_gemm_t<BM, BN, false, true>), grid, dim3(256), 0, st, p);
     else hipLaunchKernelGGL((k_gemm_t<BM, BN, false, false>), grid, dim3(256), 0, st, p);
+}
+
+// Splits of a product of one batch entry: 1, or where it would leave most
+// compute units idle at least 8 slices per split, about 512 blocks, within a
+// workspace of ws_floats
+long split_count(int M, int N, int K, int KB, long ws_floats)
+{
+    const long tiles = (long)((N + 63) / 64) * ((M + 63) / 64);
+    const long slices = (long)KB * ((K + GK - 1) / GK);
+    if (tiles >= 128 || slices < 32) return 1;
+    const long ns = std::min<long>(std::min<long>(slices / 8, (512 + tiles - 1) / tiles), 256);
+    return std::max<long>(1, std::min<long>(ns, ws_floats / ((long)M * N)));
 }
 
 // ws (ws_floats floats of device memory): where a product of one batch entry
@@ -332,19 +458,16 @@ void launch_tiled(hipStream_t st, const GemmP& p, int batch, bool ak, bool bk)
 void gemm(hipStream_t st, int batch, int M, int N, int K, int KB, const float* A, long sAm, long sAk, long sAb,
           long sAkb, const float* B, long sBk, long sBn, long sBb, long sBkb, float* C, long sCm, long sCn, long sCb,
           float alpha = 1.f, float beta = 0.f, const float* bias = nullptr, long sBiasb = 0, float* ws = nullptr,
-          long ws_floats = 0)
+          long ws_floats = 0, int epi = EPI_NONE, float* E = nullptr)
 {
     GemmP p{M, N, K, KB, A, sAm, sAk, sAb, sAkb, B, sBk, sBn, sBb, sBkb, C, sCm, sCn, sCb, alpha, beta, bias, sBiasb,
-            1, nullptr};
-    bool ak = false, bk = false;
+            1, nullptr, epi, E, sCn == 1 && N % 4 == 0 && sCm % 4 == 0 && sCb % 4 == 0 &&
+                                    !((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(E)) & 15)};
+    bool ak = false, bk = false, epi_done = false;
     if (M >= 32 && N >= 32 && K >= 16 && tiled_ok(A, sAm, sAk, sAb, sAkb, M, K, ak) &&
         tiled_ok(B, sBn, sBk, sBb, sBkb, N, K, bk)) {
-        const long tiles = (long)((N + 63) / 64) * ((M + 63) / 64);
-        const long slices = (long)KB * ((K + GK - 1) / GK);
-        if (batch == 1 && ws && tiles < 128 && slices >= 32) {
-            // at least 8 slices per split, about 512 blocks, within the workspace
-            long ns = std::min<long>(std::min<long>(slices / 8, (512 + tiles - 1) / tiles), 256);
-            ns = std::min<long>(ns, ws_floats / ((long)M * N));
+        if (batch == 1 && ws) {
+            const long ns = split_count(M, N, K, KB, ws_floats);
             if (ns >= 2) {
                 p.nsplit = (int)ns;
                 p.part = ws;
@@ -362,24 +485,160 @@ void gemm(hipStream_t st, int batch, int M, int N, int K, int KB, const float* A
         else if (M >= 128 && (long)((N + 63) / 64) * ((M + 127) / 128) * batch >= 256)
             launch_tiled<128, 64>(st, p, batch, ak, bk);
         else launch_tiled<64, 64>(st, p, batch, ak, bk);
-        return;
+        epi_done = epi_built(p, ak, bk);
+    } else {
+        hipLaunchKernelGGL(k_gemm, dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(256), 0, st, p);
     }
-    hipLaunchKernelGGL(k_gemm, dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(256), 0, st, p);
+    if (epi_done) return;
+    // (products with an epilogue are dense [batch][M][N])
+    const long n = (long)batch * M * N;
+    if (epi == EPI_GELU) hipLaunchKernelGGL(k_gelu, dim3(grid_for(n)), dim3(256), 0, st, C, E, n);
+    if (epi == EPI_GELU_BWD) hipLaunchKernelGGL(k_gelu_bwd, dim3(grid_for(n)), dim3(256), 0, st, C, E, C, n);
 }
 
 // ---------------------------------------------------------------------------
-__global__ void k_gelu(const float* __restrict__ z, float* __restrict__ y, long n)
+// Weight gradients of the whole net in two launches.  Every one is a product
+// out[m][n] = sum over samples b and times t of A[b][m][t] B[b][n][t] (rows of T
+// values, T a multiple of 32), split over blocks like gemm()'s (split_count,
+// the same partial sums); beside them the bias gradients, sums of A's rows.
+struct WJob {
+    const float *A, *B;
+    float* out;         // [M][N]
+    int M, N, ns;       // ns splits
+    int blk0;           // its first block in k_wgrad
+    int el0;            // its first block in k_wgrad_sum
+    long sA, sB;        // strides from sample to sample
+    long part;          // offset of its partial sums [ns][M][N]
+};
+struct RJob {
+    const float* X;     // [B][R][T]
+    float* out;         // [R]
+    int R, row0;        // rows, first block in k_wgrad_sum past the products'
+};
+constexpr int WJOBS = 18;   // 16 layers, lift, hidden
+struct WJobs {
+    WJob w[WJOBS];
+    RJob r[WJOBS];
+    int nw, nr, el_blocks, T, B;
+    float* part;
+};
+
+// One 64 x 64 tile of one split of one product.  Bound by the latency of its
+// few slices, so all of them go out at once: for 16 samples, width 64, 260
+// lift channels and 1024 hidden rows 1088 blocks of 8 to 16 slices, 28 us (six
+// launches of 10 to 26 us one by one).
+__global__ __launch_bounds__(256) void k_wgrad(WJobs js)
 {
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-        y[i] = gelu_f(z[i]);
+    constexpr int GLD = GK + 8;
+    __shared__ __attribute__((aligned(16))) __bf16 As[64][GLD];
+    __shared__ __attribute__((aligned(16))) __bf16 Bs[64][GLD];
+    int q = 0;
+    while (q + 1 < js.nw && (int)blockIdx.x >= js.w[q + 1].blk0) ++q;
+    const WJob& j = js.w[q];
+    const int nn = (j.N + 63) / 64, tiles = nn * ((j.M + 63) / 64);
+    const int rem = xcd_item(blockIdx.x - j.blk0, j.ns * tiles), z = rem / tiles, tile = rem - z * tiles;
+    const int m0 = tile / nn * 64, n0 = tile % nn * 64;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+    f4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) acc[i][k] = f4{0.f, 0.f, 0.f, 0.f};
+    Slice<64, true> sa, sb;
+    const int nks = js.T / GK;
+    const long ns = (long)nks * js.B;
+    const int s_lo = (int)(ns * z / j.ns), s_hi = (int)(ns * (z + 1) / j.ns);
+    auto load = [&](int s) {
+        const int kb = s / nks, k0 = (s - kb * nks) * GK;
+        sa.load(j.A + kb * j.sA, js.T, 1, j.M, js.T, m0, k0);
+        sb.load(j.B + kb * j.sB, js.T, 1, j.N, js.T, n0, k0);
+    };
+    if (s_lo < s_hi) load(s_lo);
+    for (int s = s_lo; s < s_hi; ++s) {
+        sa.store(As);
+        sb.store(Bs);
+        __syncthreads();
+        if (s + 1 < s_hi) load(s + 1);
+        bf8 av[2], bv[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            av[i] = *reinterpret_cast<const bf8*>(&As[wm + i * 16 + (lane & 15)][swz(wm + i * 16, 8 * (lane >> 4))]);
+            bv[i] = *reinterpret_cast<const bf8*>(&Bs[wn + i * 16 + (lane & 15)][swz(wn + i * 16, 8 * (lane >> 4))]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[k], acc[i][k], 0, 0, 0);
+        __syncthreads();
+    }
+    float* __restrict__ P = js.part + j.part + (long)z * j.M * j.N;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = m0 + wm + i * 16 + 4 * (lane >> 4) + e;
+                const int col = n0 + wn + k * 16 + (lane & 15);
+                if (row < j.M && col < j.N) P[(long)row * j.N + col] = acc[i][k][e];
+            }
 }
 
-__global__ void k_gelu_bwd(const float* __restrict__ dy, const float* __restrict__ z, float* __restrict__ dz, long n)
+// Partial sums added up in split order, and bias gradients (k_rowsum's order).
+// Each output is one serial chain of adds; its loads go out 16 at a time: 30 us
+// for the whole net (16 to 23 us for each of 12 launches).
+__global__ __launch_bounds__(256) void k_wgrad_sum(WJobs js)
 {
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-        dz[i] = dy[i] * gelu_d(z[i]);
+    __shared__ float red[256];
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < js.el_blocks) {
+        int q = 0;
+        while (q + 1 < js.nw && (int)blockIdx.x >= js.w[q + 1].el0) ++q;
+        const WJob& j = js.w[q];
+        const long n = (long)j.M * j.N, e = (long)(blockIdx.x - j.el0) * 256 + tid;
+        if (e >= n) return;
+        const float* __restrict__ P = js.part + j.part + e;
+        float acc = 0.f;
+        int z = 0;
+        for (; z + 16 <= j.ns; z += 16) {
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = P[(z + i) * n];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc += v[i];
+        }
+        for (; z < j.ns; ++z) acc += P[z * n];
+        j.out[e] = acc;
+        return;
+    }
+    const int row = blockIdx.x - js.el_blocks;
+    int q = 0;
+    while (q + 1 < js.nr && row >= js.r[q + 1].row0) ++q;
+    const RJob& r = js.r[q];
+    const int m = row - r.row0, T = js.T, per = (T + 255) / 256, cnt = js.B * per;
+    float s = 0.f;
+    for (int i0 = 0; i0 < cnt; i0 += 16) {
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int c = i0 + i, b = c / per, t = (c - b * per) * 256 + tid;
+            v[i] = c < cnt && t < T ? r.X[((long)b * r.R + m) * T + t] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (i0 + i < cnt) s += v[i];
+    }
+    red[tid] = s;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if (tid < h) red[tid] += red[tid + h];
+        __syncthreads();
+    }
+    if (tid == 0) r.out[m] = red[0];
 }
 
+// ---------------------------------------------------------------------------
 struct Feat {
     float off[9], inv[9];
     float cyc[SNO_MAX_FOUR];   // Fourier feature frequencies, cycles per window
@@ -670,35 +929,6 @@ __global__ __launch_bounds__(256) void k_fcomb(const float* __restrict__ Yf, con
     }
 }
 
-// dYf[b][f O + o][i] = sum_t dY[b][o][t] w_{t,i}: the transpose of k_fcomb, as a
-// gather over the (at most five) t whose interpolation reads sample i
-__global__ __launch_bounds__(256) void k_fspread(const float* __restrict__ dY, const float* __restrict__ shift, int B,
-                                                 int F, int O, int n_rec, int T, float* __restrict__ dYf)
-{
-    // block rows ((b F + f) O + o), threads along i
-    for (int row = blockIdx.y; row < B * F * O; row += gridDim.y) {
-        const int o = row % O, bf = row / O, b = bf / F;
-        const float sh = shift[bf * n_rec + o % n_rec];
-        const float* __restrict__ g = dY + ((long)b * O + o) * T;
-        for (int i = blockIdx.x * 256 + threadIdx.x; i < T; i += gridDim.x * 256) {
-            // t - sh in [i - 2, i + 1] reads sample i
-            const int t0 = max(0, (int)floorf((float)i - 2.f + sh));
-            const int t1 = min(T - 1, (int)ceilf((float)i + 1.f + sh));
-            float acc = 0.f;
-            for (int t = t0; t <= t1; ++t) {
-                const float x = (float)t - sh;
-                const float fl = floorf(x);
-                const int k = i - (int)fl + 1;
-                if (k < 0 || k > 3) continue;
-                float c[4];
-                lagrange4(x - fl, c);
-                acc += c[k] * g[t];
-            }
-            dYf[(long)row * T + i] = acc;
-        }
-    }
-}
-
 // Per-mode complex channel mixing of the spectral layers (16 modes, width C):
 // U[b][c][k] = sum_c' M_k[c][c'] V[b][c'][k] with M_k = Rr_k + i Ri_k
 // (forward) or its conjugate transpose (the input gradient), real parts at
@@ -830,34 +1060,123 @@ __global__ __launch_bounds__(256) void k_rowsum(const float* __restrict__ X, int
     if (threadIdx.x == 0) out[r] = red[0];
 }
 
-// dY = 2 (Y - Yt) / n; block partial sums of (Y - Yt)^2
-// dY = 2 w (Y - Yt) / n and per-block partial sums of w (Y - Yt)^2, with w
-// = wgt[b][o / n_rec] per sample and component (1 without weights); rows
-// (b, o) in a fixed order per block, so the partial sums are reproducible
-__global__ __launch_bounds__(256) void k_mse(const float* __restrict__ Y, const float* __restrict__ Yt,
-                                             const float* __restrict__ wgt, int B, int O, int T, int n_rec,
-                                             float* __restrict__ dY, float* __restrict__ part)
+// Gradient of the loss to the frames, one block per output row (b, o) at a time:
+//   dY[t] = 2 w (Y - Yt) / n, with w = wgt[b][o / n_rec] (1 without weights);
+//   dYf[b][f O + o][i] = sum_t dY[t] w_{t,i}, the transpose of k_fcomb, as a
+//   gather over the (at most five) t whose interpolation reads sample i (one
+//   frame: dYf = dY); dbm = the sums of dYf's rows; part[row] = the row's share
+//   of the loss.
+// dY stays in LDS, and with it the interpolation weights of the t that a
+// segment of SPREAD samples reads, formed once per t and frame.  With
+// floor(t - shift) = t + K for all of them (rounding of t - shift can break it
+// where it crosses a power of two: then each sample looks for its t) sample i
+// reads t = i - 2 - K to i + 1 - K with weights 3 to 0.  16 samples of 256 series
+// of 1024, two frames: 87 us as three passes over memory that formed the
+// weights once per t and sample, 44 with the search for each sample's t, 35 so.
+constexpr int SPREAD = 1024, SPREAD_T = SPREAD + 3;
+
+__device__ __forceinline__ float block_tree(float s, float* red)
 {
-    __shared__ float red[256];
-    float s = 0.f;
-    const float g = 2.f / ((float)B * O * T);
-    for (int row = blockIdx.x; row < B * O; row += gridDim.x) {
-        const int b = row / O, o = row - b * O;
-        const float w = wgt ? wgt[b * 4 + o / n_rec] : 1.f;
-        const long base = (long)row * T;
-        for (int t = threadIdx.x; t < T; t += 256) {
-            const float d = Y[base + t] - Yt[base + t];
-            dY[base + t] = g * w * d;
-            s += w * d * d;
-        }
-    }
     red[threadIdx.x] = s;
     __syncthreads();
     for (int h = 128; h > 0; h >>= 1) {
         if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    return red[0];
+}
+
+__global__ __launch_bounds__(256) void k_loss_grad(const float* __restrict__ Y, const float* __restrict__ Yt,
+                                                   const float* __restrict__ wgt, const float* __restrict__ shift, int B,
+                                                   int F, int O, int n_rec, int T, float* __restrict__ dYf,
+                                                   float* __restrict__ dbm, float* __restrict__ part)
+{
+    __shared__ float red[256];
+    __shared__ float cs[4][SPREAD_T];
+    __shared__ float gq[SPREAD_T];
+    extern __shared__ float gs[];   // dY of the row
+    const int tid = threadIdx.x;
+    const float g = 2.f / ((float)B * O * T);
+    for (int row = blockIdx.x; row < B * O; row += gridDim.x) {
+        const int b = row / O, o = row - b * O;
+        const float w = wgt ? wgt[b * 4 + o / n_rec] : 1.f;
+        const long base = (long)row * T;
+        float s = 0.f, rs = 0.f;
+        for (int t = tid; t < T; t += 256) {
+            const float d = Y[base + t] - Yt[base + t];
+            const float v = g * w * d;
+            gs[t] = v;
+            s += w * d * d;
+            if (F == 1) {
+                dYf[base + t] = v;
+                rs += v;
+            }
+        }
+        s = block_tree(s, red);
+        if (tid == 0) part[row] = s;
+        __syncthreads();
+        if (F == 1) {
+            rs = block_tree(rs, red);
+            if (tid == 0) dbm[row] = rs;
+            __syncthreads();
+            continue;
+        }
+        for (int f = 0; f < F; ++f) {
+            const long fo = (long)(b * F + f) * O + o;
+            const float sh = shift[(b * F + f) * n_rec + o % n_rec];
+            rs = 0.f;
+            for (int i0 = 0; i0 < T; i0 += SPREAD) {
+                const int i1 = min(i0 + SPREAD, T);
+                const bool small = fabsf(sh) < 1e6f;
+                const int K = small ? (int)floorf(-sh) : 0, ta = i0 - 2 - K;
+                bool ok = small;
+                for (int q = tid; q < i1 - i0 + 3; q += 256) {
+                    const int t = ta + q;
+                    const bool in = t >= 0 && t < T;
+                    const float x = (float)t - sh;
+                    const float fl = floorf(x);
+                    float c[4];
+                    lagrange4(x - fl, c);
+                    ok = ok && (!in || (int)fl == t + K);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) cs[k][q] = in ? c[k] : 0.f;
+                    gq[q] = in ? gs[t] : 0.f;
+                }
+                if (__syncthreads_and(ok)) {
+                    for (int i = i0 + tid; i < i1; i += 256) {
+                        const int q = i - i0;
+                        float acc = 0.f;
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) acc += cs[3 - d][q + d] * gq[q + d];
+                        dYf[fo * T + i] = acc;
+                        rs += acc;
+                    }
+                } else {
+                    for (int i = i0 + tid; i < i1; i += 256) {
+                        // t - sh in [i - 2, i + 1] reads sample i
+                        const int t0 = max(0, (int)floorf((float)i - 2.f + sh));
+                        const int t1 = min(T - 1, (int)ceilf((float)i + 1.f + sh));
+                        float acc = 0.f;
+                        for (int t = t0; t <= t1; ++t) {
+                            const float x = (float)t - sh;
+                            const float fl = floorf(x);
+                            const int k = i - (int)fl + 1;
+                            if (k < 0 || k > 3) continue;
+                            float c[4];
+                            lagrange4(x - fl, c);
+                            acc += c[k] * gs[t];
+                        }
+                        dYf[fo * T + i] = acc;
+                        rs += acc;
+                    }
+                }
+                __syncthreads();
+            }
+            rs = block_tree(rs, red);
+            if (tid == 0) dbm[fo] = rs;
+            __syncthreads();
+        }
+    }
 }
 
 // relative-loss weights of n samples: w[i][c] = 1 / mean square of sample i's
@@ -891,13 +1210,14 @@ __global__ void k_gather_w(const float* __restrict__ w, const int* __restrict__ 
     if (e < B * 4) wb[e] = w[idx[e / 4] * 4 + e % 4];
 }
 
-__global__ void k_sum_parts(const float* __restrict__ part, int np, float* __restrict__ out, float scale)
+__global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ part, int np, float* __restrict__ out,
+                                                   float scale)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        float s = 0.f;
-        for (int i = 0; i < np; ++i) s += part[i];
-        *out = s * scale;
-    }
+    __shared__ float red[256];
+    float s = 0.f;
+    for (int i = threadIdx.x; i < np; i += 256) s += part[i];
+    s = block_tree(s, red);
+    if (threadIdx.x == 0) *out = s * scale;
 }
 
 // Adam step; omb1 = 1 - b1 and omb2 = 1 - b2 come rounded from double (1 - b2
@@ -1067,7 +1387,6 @@ __global__ void k_decim(const float* __restrict__ in, long rows, int nt, int dec
     }
 }
 
-int grid_for(long n) { return (int)std::min<long>((n + 255) / 256, 4096); }
 // 256-thread blocks along a row of `len` values, one block row per row (the
 // kernels loop over rows past the grid's y limit)
 dim3 rows_grid(long len, long rows)
@@ -1114,7 +1433,8 @@ struct sno {
     float *iV[2] = {nullptr, nullptr}, *iVh = nullptr, *iUh = nullptr, *ipool = nullptr, *iQm = nullptr, *ibm = nullptr,
           *iY = nullptr, *ishift = nullptr;
     // partial sums of the split weight-gradient products
-    static constexpr long kws_n = 4L << 20;
+    static constexpr long kws_n = 4L << 20;    // of one product
+    static constexpr long kws_all = 8L << 20;   // of products that go out together
     float* kws = nullptr;
     float* wb = nullptr;       // the batch's loss weights [B][4]
 
@@ -1164,8 +1484,8 @@ struct sno {
             al(&Uh, (long)B * C * K2) || al(&Hp, (long)B * H * T) || al(&Hq, (long)B * H * T) ||
             al(&Y, (long)B * O * T) || al(&X0, (long)B * std::max(C, (long)O) * T) || al(&X1, (long)B * C * T) ||
             al(&X2, (long)B * C * T) || al(&dH, (long)B * H * T) || al(&dUh, (long)B * C * K2) ||
-            al(&dVh, (long)B * C * K2) || al(&part, 4096) || al(&lossd, 4) || al(&phi, (long)B * (C + 7)) ||
-            al(&Xb, (long)B * 9) || al(&Yb, (long)B * O * T) || al(&kws, kws_n) || al(&wb, (long)B * 4) ||
+            al(&dVh, (long)B * C * K2) || al(&part, (long)B * O) || al(&lossd, 4) || al(&phi, (long)B * (C + 7)) ||
+            al(&Xb, (long)B * 9) || al(&Yb, (long)B * O * T) || al(&kws, kws_all) || al(&wb, (long)B * 4) ||
             hipMalloc(&idxd, B * sizeof(int)))
             return sfail(PSTD_ENOMEM, "surrogate workspace");
         bmax = B;
@@ -1263,11 +1583,12 @@ bool cfg_ok(const sno_cfg* c)
 
 // The fused kernels' range: the widths they are built for, up to 16 modes,
 // whole 128-sample tiles of time and 32-deep slices of hidden rows, float4
-// operands.  Everything else goes through the general GEMM.
+// operands (lift channels that the general path too adds up in one order: 4,
+// or 16 and more).  Everything else goes through the general GEMM.
 bool fused_ok(const sno* s)
 {
     const sno_cfg& c = s->cfg;
-    return (c.C == 32 || c.C == 64) && c.K >= 8 && c.K <= 16 && c.K % 2 == 0 && c.T % 128 == 0 && s->NA >= 16 &&
+    return (c.C == 32 || c.C == 64) && c.K >= 8 && c.K <= 16 && c.K % 2 == 0 && c.T % 128 == 0 && (s->NA >= 16 || s->NA == 4) &&
            s->NA % 4 == 0 && c.H % 32 == 0 && s->F * s->O >= 32;
 }
 
@@ -1290,13 +1611,13 @@ void trunk_c(sno* s, hipStream_t st, const float* X, int B, int TS, float* A, fl
     const dim3 tiles(T / 64, B);
     hipLaunchKernelGGL((snof::k_lift<C>), tiles, dim3(256), (size_t)lp.rows * 64 * sizeof(float), st, lp);
     for (int l = 0; l < c.L; ++l) {
-        if (K2 >= 32) snof::launch_dft<32, false>(st, B, V[l], nullptr, nullptr, s->Ft, C, T, TS, K2, Vh[l]);
-        else snof::launch_dft<16, false>(st, B, V[l], nullptr, nullptr, s->Ft, C, T, TS, K2, Vh[l]);
+        if (K2 >= 32) snof::launch_dft<32>(st, B, V[l], s->Ft, C, T, TS, K2, Vh[l]);
+        else snof::launch_dft<16>(st, B, V[l], s->Ft, C, T, TS, K2, Vh[l]);
         hipLaunchKernelGGL((snof::k_cmix_f<C>), dim3(c.K, (B + snof::MB - 1) / snof::MB, C / 32), dim3(256), 0, st,
                            th + s->off_Rr[l], th + s->off_Ri[l], Vh[l], B, c.K, Uh);
         const bool last = l == c.L - 1;
         const snof::ZP zp{th + s->off_W[l], th + s->off_b[l], V[l], Uh, s->Gt, T, TS, K2,
-                          last ? V[l + 1] : Z ? Z[l] : nullptr, last ? nullptr : V[l + 1], last ? pool : nullptr};
+                          last ? V[l + 1] : Z ? Z[l] : nullptr, last ? nullptr : V[l + 1], last ? pool : nullptr, nullptr};
         hipLaunchKernelGGL((snof::k_zlayer<C, false>), tiles, dim3(256), 0, st, zp);
     }
 }
@@ -1429,8 +1750,7 @@ void forward(sno* s, hipStream_t st, const float* X, int B)
         }
     }
     gemm(st, B, H, T, C, 1, th + s->off_Q1, C, 1, 0, 0, s->V(c.L), T, 1, C * T, 0, s->Hp, T, 1, H * T, 1.f, 0.f,
-         th + s->off_q1b);
-    hipLaunchKernelGGL(k_gelu, dim3(grid_for(B * H * T)), dim3(256), 0, st, s->Hp, s->Hq, (long)B * H * T);
+         th + s->off_q1b, 0, nullptr, 0, EPI_GELU, s->Hq);
     // moment-weighted projection: one frame writes the output directly, two
     // frames go through the per-receiver delays
     const long FO = s->F * O;
@@ -1448,6 +1768,77 @@ void forward(sno* s, hipStream_t st, const float* X, int B)
     }
 }
 
+// The rest of the backward pass, from dH, through the fused kernels: per layer
+// the transposed inverse DFT, the mixing with its weight gradients, and both
+// products of dV with the derivative of the activation below; dZ takes the
+// place of Z.  The
+// weight gradients of all layers, the lift and the hidden map follow together.
+template <int C>
+void backward_trunk(sno* s, hipStream_t st, int B)
+{
+    const sno_cfg& c = s->cfg;
+    const int T = c.T, K2 = 2 * c.K, H = c.H, NA = s->NA;
+    const float* th = s->theta;
+    float* g = s->grad;
+    WJobs js{};
+    js.T = T;
+    js.B = B;
+    js.part = s->kws;
+    long part = 0;
+    int blk = 0, row = 0;
+    auto flush = [&]() {
+        if (js.nw) hipLaunchKernelGGL(k_wgrad, dim3(blk), dim3(256), 0, st, js);
+        if (js.nw || js.nr) hipLaunchKernelGGL(k_wgrad_sum, dim3(js.el_blocks + row), dim3(256), 0, st, js);
+        js.nw = js.nr = js.el_blocks = blk = row = 0;
+        part = 0;
+    };
+    // weight gradient A B^T, and the row sums of A
+    auto wgrad = [&](const float* A, int M, const float* Bm, int N, float* out, float* bias) {
+        const long ns = split_count(M, N, T, B, sno::kws_n), need = ns * M * N;
+        if (M < 32 || N < 32 || ns < 2) {
+            gemm(st, 1, M, N, T, B, A, T, 1, 0, (long)M * T, Bm, 1, T, 0, (long)N * T, out, N, 1, 0);
+        } else {
+            if (part + need > sno::kws_all) flush();
+            const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
+            js.w[js.nw++] = WJob{A, Bm, out, M, N, (int)ns, blk, js.el_blocks, (long)M * T, (long)N * T, part};
+            part += need;
+            blk += (int)ns * tiles;
+            js.el_blocks += (int)(((long)M * N + 255) / 256);
+        }
+        js.r[js.nr++] = RJob{A, bias, M, row};
+        row += M;
+    };
+    wgrad(s->dH, H, s->V(c.L), C, g + s->off_Q1, g + s->off_q1b);
+    // (the last layer has no activation)
+    float* dZ = s->X1;
+    gemm(st, B, C, T, H, 1, th + s->off_Q1, 1, C, 0, 0, s->dH, T, 1, (long)H * T, 0, dZ, T, 1, (long)C * T);
+    for (int l = c.L - 1; l >= 0; --l) {
+        if (K2 >= 32) snof::launch_dft<32>(st, B, dZ, s->G, C, T, T, K2, s->dUh);
+        else snof::launch_dft<16>(st, B, dZ, s->G, C, T, T, K2, s->dUh);
+        const int nmix = (B + snof::MB - 1) / snof::MB * (C / 32);
+        hipLaunchKernelGGL((snof::k_cmix_b<C>), dim3(c.K, nmix + C / snof::DWC), dim3(256), 0, st, th + s->off_Rr[l],
+                           th + s->off_Ri[l], s->dUh, s->Vhl(l), B, c.K, nmix, s->dVh, g + s->off_Rr[l],
+                           g + s->off_Ri[l]);
+        // dV = W^T dZ + dVh F^T, times the derivative of the layer below's activation
+        float* below = l > 0 ? s->Zl(l - 1) : s->X2;
+        const snof::ZP zp{th + s->off_W[l], nullptr, dZ, s->dVh, s->Fb, T, T, K2, below, nullptr, nullptr,
+                          l > 0 ? below : nullptr};
+        hipLaunchKernelGGL((snof::k_zlayer<C, true>), dim3(T / 64, B), dim3(256), 0, st, zp);
+        wgrad(dZ, C, s->V(l), C, g + s->off_W[l], g + s->off_b[l]);
+        dZ = below;
+    }
+    if (NA < 32) {
+        // a small product that the general path would form in one block per
+        // 64 channels, 16 values at a time
+        snof::launch_dft<16, true>(st, B, dZ, s->A, C, T, T, NA, g + s->off_P);
+        js.r[js.nr++] = RJob{dZ, g + s->off_pb, C, row};
+        row += C;
+    } else {
+        wgrad(dZ, C, s->A, NA, g + s->off_P, g + s->off_pb);
+    }
+    flush();
+}
+
 // gradient of the mean squared error of s->Y against Yt (after the forward of
 // the same features X)
 void backward(sno* s, hipStream_t st, const float* X, const float* Yt, int B, const float* wgt = nullptr)
@@ -1456,26 +1847,24 @@ void backward(sno* s, hipStream_t st, const float* X, const float* Yt, int B, co
     const long C = c.C, T = c.T, K = c.K, K2 = 2 * K, H = c.H, O = s->O;
     const float* th = s->theta;
     float* g = s->grad;
-    const long nY = (long)B * O * T;
-    float* dY = s->X0;
-    hipLaunchKernelGGL(k_mse, dim3(256), dim3(256), 0, st, s->Y, Yt, wgt, B, (int)O, (int)T, c.n_rec, dY, s->part);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, st, s->part, 256, s->lossd, 1.f / (float)nY);
-    // frame delays (transposed), then the moment-weighted projection:
+    const long nY = (long)B * O * T, FO = s->F * O;
+    // the loss, frame delays (transposed), then the moment-weighted projection:
     // dQm[b] = dYf[b] Hq[b]^T, dbm[b] = row sums of dYf[b], dHq[b] = Qm[b]^T dYf[b],
     // and the 6 responses' gradients weighted back by the moment features
-    const long FO = s->F * O;
-    float* dYf = dY;
-    if (s->F == 2) {
-        dYf = s->dY6;
-        hipLaunchKernelGGL(k_fspread, rows_grid(T, B * FO), dim3(256), 0, st, dY, s->shift, B, s->F, (int)O, c.n_rec,
-                           (int)T, dYf);
-    }
+    float* dYf = s->dY6;
+    hipLaunchKernelGGL(k_loss_grad, dim3((unsigned)std::min<long>(B * O, 65535)), dim3(256), T * sizeof(float), st, s->Y,
+                       Yt, wgt, s->shift, B, s->F, (int)O, c.n_rec, (int)T, dYf, s->dbm, s->part);
+    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, st, s->part, (int)(B * O), s->lossd, 1.f / (float)nY);
     gemm(st, B, FO, H, T, 1, dYf, T, 1, FO * T, 0, s->Hq, 1, T, H * T, 0, s->dQm, H, 1, FO * H);
-    hipLaunchKernelGGL(k_rowsum, dim3(B * FO), dim3(256), 0, st, dYf, 1, (int)(B * FO), (int)T, s->dbm);
     hipLaunchKernelGGL(k_qgrad, rows_grid(H + 1, FO), dim3(256), 0, st, s->dQm, s->dbm, X, s->feat, B, (int)FO, (int)O,
                        (int)H, g + s->off_Q2, g + s->off_q2b);
-    gemm(st, B, H, T, FO, 1, s->Qm, 1, H, FO * H, 0, dYf, T, 1, FO * T, 0, s->dH, T, 1, H * T);
-    hipLaunchKernelGGL(k_gelu_bwd, dim3(grid_for(B * H * T)), dim3(256), 0, st, s->dH, s->Hp, s->dH, (long)B * H * T);
+    gemm(st, B, H, T, FO, 1, s->Qm, 1, H, FO * H, 0, dYf, T, 1, FO * T, 0, s->dH, T, 1, H * T, 1.f, 0.f, nullptr, 0,
+         nullptr, 0, EPI_GELU_BWD, s->Hp);
+    if (s->fused) {
+        if (c.C == 64) backward_trunk<64>(s, st, B);
+        else backward_trunk<32>(s, st, B);
+        return;
+    }
     gemm(st, 1, H, C, T, B, s->dH, T, 1, 0, H * T, s->V(c.L), 1, T, 0, C * T, g + s->off_Q1, C, 1, 0, 1.f, 0.f, nullptr, 0, s->kws, s->kws_n);
     hipLaunchKernelGGL(k_rowsum, dim3(H), dim3(256), 0, st, s->dH, B, (int)H, (int)T, g + s->off_q1b);
     float* bufs[3] = {s->X1, s->X2, s->X0};

@@ -137,14 +137,14 @@ __device__ __forceinline__ float gelu_d(float x)
 // threads load TC time samples of V and of the transposed basis at once,
 // round them into LDS in operand order, and while two waves run the chain over
 // them (one per 16 columns) the next TC are on their way.  KS: k per MFMA, 32,
-// or 16 where K2 < 32 (the general path's choice there).  With GB the input is
-// dZ = V gelu'(Zp) (Zp the pre-activation), which is also written to dZ.
+// or 16 where K2 < 32 (the general path's choice there).  SUM: Ft is given per
+// sample, [B][K2][T], and the chain runs on over the samples to Vh[c][q] (a
+// narrow weight gradient).
 // 16 x 1024 by 32 columns, one sample: 4.7 us (26 us as a general 64 x 64
 // tile, one block per sample, one slice in flight); 256 samples 22 us, 3 TB/s.
-template <int KS, int TC, bool GB>
-__global__ __launch_bounds__(256) void k_dft(const float* __restrict__ V, const float* __restrict__ Zp,
-                                             float* __restrict__ dZ, const float* __restrict__ Ft, int C, int T, int TS,
-                                             int K2, float* __restrict__ Vh)
+template <int KS, int TC, bool SUM>
+__global__ __launch_bounds__(256) void k_dft(const float* __restrict__ V, const float* __restrict__ Ft, int B, int C,
+                                             int T, int TS, int K2, float* __restrict__ Vh)
 {
     // operand chunks of KS / 4 values (one lane's k of a slice) by 16 rows,
     // with spare bytes so that the stores of one row spread over the banks
@@ -154,35 +154,29 @@ __global__ __launch_bounds__(256) void k_dft(const float* __restrict__ V, const 
     constexpr int VA = TC / 64, VB = TC / 32;   // float4 per thread
     const int b = blockIdx.y, c0 = blockIdx.x * 16;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 15, g = lane >> 4;
-    float4 va[VA], vb[VB], vz[GB ? VA : 1];
-    const long base = ((long)b * C + c0) * TS;
-    auto load = [&](int t) {
+    float4 va[VA], vb[VB];
+    auto load = [&](int b, int t) {
+        const long base = ((long)b * C + c0) * TS;
+        const float* __restrict__ F = Ft + (SUM ? (long)b * K2 * T : 0L);
 #pragma unroll
         for (int i = 0; i < VA; ++i) {
             const int e = tid + i * 256, row = e / (TC / 4), q = (e % (TC / 4)) * 4;
             va[i] = ld4(V + base + (long)row * TS + t + q);
-            if constexpr (GB) vz[i] = ld4(Zp + base + (long)row * TS + t + q);
         }
 #pragma unroll
         for (int i = 0; i < VB; ++i) {
             const int e = tid + i * 256, row = e / (TC / 4), q = (e % (TC / 4)) * 4;
-            vb[i] = ld4(Ft + (long)min(row, K2 - 1) * T + t + q);   // rows past K2 are not stored
+            vb[i] = ld4(F + (long)min(row, K2 - 1) * T + t + q);   // rows past K2 are not stored
         }
     };
     f4 acc = {0.f, 0.f, 0.f, 0.f};
-    load(0);
-    for (int t = 0; t < T; t += TC) {   // T is a multiple of TC
-        if (t > 0) __syncthreads();
+    const int b_hi = SUM ? B - 1 : b;
+    load(b, 0);
+    for (int bb = b, t = 0; bb <= b_hi;) {   // T is a multiple of TC
+        if (bb > b || t > 0) __syncthreads();
 #pragma unroll
         for (int i = 0; i < VA; ++i) {
             const int e = tid + i * 256, row = e / (TC / 4), q = (e % (TC / 4)) * 4;
-            if constexpr (GB) {
-                va[i].x *= gelu_d(vz[i].x);
-                va[i].y *= gelu_d(vz[i].y);
-                va[i].z *= gelu_d(vz[i].z);
-                va[i].w *= gelu_d(vz[i].w);
-                *reinterpret_cast<float4*>(dZ + base + (long)row * TS + t + q) = va[i];
-            }
             *reinterpret_cast<bf4*>(As + q / CH * ST + row * CH + q % CH) = cvt4(va[i].x, va[i].y, va[i].z, va[i].w);
         }
 #pragma unroll
@@ -191,7 +185,13 @@ __global__ __launch_bounds__(256) void k_dft(const float* __restrict__ V, const 
             *reinterpret_cast<bf4*>(Bs[row >> 4] + q / CH * ST + (row & 15) * CH + q % CH) =
                 cvt4(vb[i].x, vb[i].y, vb[i].z, vb[i].w);
         }
-        load(min(t + TC, T - TC));
+        t += TC;
+        if (SUM && t == T) {
+            t = 0;
+            ++bb;
+        }
+        load(min(bb, b_hi), min(t, T - TC));
+        if (!SUM && t == T) ++bb;
         __syncthreads();
         if (w < 2 && w * 16 < K2) {
 #pragma unroll 8
@@ -210,13 +210,12 @@ __global__ __launch_bounds__(256) void k_dft(const float* __restrict__ V, const 
         for (int i = 0; i < 4; ++i) Vh[((long)b * C + c0 + 4 * g + i) * K2 + w * 16 + r] = acc[i];
 }
 
-template <int KS, bool GB>
-inline void launch_dft(hipStream_t st, int B, const float* V, const float* Zp, float* dZ, const float* Ft, int C, int T,
-                       int TS, int K2, float* Vh)
+template <int KS, bool SUM = false>
+inline void launch_dft(hipStream_t st, int B, const float* V, const float* Ft, int C, int T, int TS, int K2, float* Vh)
 {
-    const dim3 grid(C / 16, B);
-    if (T % 512 == 0) hipLaunchKernelGGL((k_dft<KS, 512, GB>), grid, dim3(256), 0, st, V, Zp, dZ, Ft, C, T, TS, K2, Vh);
-    else hipLaunchKernelGGL((k_dft<KS, 128, GB>), grid, dim3(256), 0, st, V, Zp, dZ, Ft, C, T, TS, K2, Vh);
+    const dim3 grid(C / 16, SUM ? 1 : B);
+    if (T % 512 == 0) hipLaunchKernelGGL((k_dft<KS, 512, SUM>), grid, dim3(256), 0, st, V, Ft, B, C, T, TS, K2, Vh);
+    else hipLaunchKernelGGL((k_dft<KS, 128, SUM>), grid, dim3(256), 0, st, V, Ft, B, C, T, TS, K2, Vh);
 }
 
 // ---------------------------------------------------------------------------
@@ -291,19 +290,92 @@ __global__ __launch_bounds__(256) void k_cmix_f(const float* __restrict__ Rr, co
     cmix_block<C, false>(Rr, Ri, V, B, K, U, blockIdx.x, blockIdx.y * MB, blockIdx.z * 32, sm);
 }
 
+// Gradient of the mixing weights of mode k, rows c0 to c0 + DWC, summed over the
+// samples (ascending, one chain of FMA per output):
+// dRr[c][q] = sum_b dUr[b][c] Vr[b][q] + dUi[b][c] Vi[b][q],
+// dRi[c][q] = sum_b dUi[b][c] Vr[b][q] - dUr[b][c] Vi[b][q].
+constexpr int DWC = 16, DWB = 32;
+
+template <int C>
+__device__ __forceinline__ void cmix_dw_block(const float* __restrict__ dU, const float* __restrict__ V, int B, int K,
+                                              float* __restrict__ dRr, float* __restrict__ dRi, int k, int c0, float* sm)
+{
+    float(*ur)[DWC] = reinterpret_cast<float(*)[DWC]>(sm);
+    float(*ui)[DWC] = reinterpret_cast<float(*)[DWC]>(sm + DWB * DWC);
+    float(*vr)[C] = reinterpret_cast<float(*)[C]>(sm + 2 * DWB * DWC);
+    float(*vi)[C] = reinterpret_cast<float(*)[C]>(sm + 2 * DWB * DWC + DWB * C);
+    constexpr int PER = DWC * C / 256;
+    const int tid = threadIdx.x, q = tid % C, cq = tid / C * PER;
+    const long K2 = 2L * K;
+    float ar[PER], ai[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) ar[j] = ai[j] = 0.f;
+    for (int b0 = 0; b0 < B; b0 += DWB) {
+        const int nb = min(DWB, B - b0);
+        __syncthreads();
+        for (int e = tid; e < nb * C; e += 256) {
+            const int b = e / C, r = e % C;
+            const long at = ((long)(b0 + b) * C + r) * K2 + k;
+            vr[b][r] = V[at];
+            vi[b][r] = V[at + K];
+        }
+        for (int e = tid; e < nb * DWC; e += 256) {
+            const int b = e / DWC, r = e % DWC;
+            const long at = ((long)(b0 + b) * C + c0 + r) * K2 + k;
+            ur[b][r] = dU[at];
+            ui[b][r] = dU[at + K];
+        }
+        __syncthreads();
+        for (int b = 0; b < nb; ++b) {
+            const float yr = vr[b][q], yi = vi[b][q];
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const float xr = ur[b][cq + j], xi = ui[b][cq + j];
+                ar[j] = fmaf(xr, yr, fmaf(xi, yi, ar[j]));
+                ai[j] = fmaf(xi, yr, fmaf(-xr, yi, ai[j]));
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const long at = ((long)k * C + c0 + cq + j) * C + q;
+        dRr[at] = ar[j];
+        dRi[at] = ai[j];
+    }
+}
+
+// Backward mixing: grid (K, nmix + C / DWC), the first nmix blocks of a mode
+// form dV = M^H dU (as k_cmix_f), the others the weight gradients.  16 samples
+// of width 64: 128 blocks instead of two launches of 16 (46 us).
+template <int C>
+__global__ __launch_bounds__(256) void k_cmix_b(const float* __restrict__ Rr, const float* __restrict__ Ri,
+                                                const float* __restrict__ dU, const float* __restrict__ Vh, int B, int K,
+                                                int nmix, float* __restrict__ dVh, float* __restrict__ dRr,
+                                                float* __restrict__ dRi)
+{
+    constexpr int N0 = cmix_lds<C>(), N1 = 2 * DWB * (DWC + C);
+    __shared__ float sm[N0 > N1 ? N0 : N1];
+    const int y = blockIdx.y;
+    if (y < nmix) cmix_block<C, true>(Rr, Ri, dU, B, K, dVh, blockIdx.x, y / (C / 32) * MB, y % (C / 32) * 32, sm);
+    else cmix_dw_block<C>(dU, Vh, B, K, dRr, dRi, blockIdx.x, (y - nmix) * DWC, sm);
+}
+
 // ---------------------------------------------------------------------------
 // Pointwise map, inverse DFT of the mixed modes and activation of one layer:
 //   Z[b][c][t] = (sum_q W[c][q] V[b][q][t] + bias[c]) + sum_k Uh[b][c][k] Gt[t][k]
 //   Vn = gelu(Z)
 // for 64 time samples of one sample per block; either output may be null.
 // pool (last layer, may be null): pool[b][blockIdx.x][c] = sum over the
-// block's 64 t of Z.  TRW: W is read transposed (the backward pass).  Bound
+// block's 64 t of Z.  TRW: W is read transposed, and Z is multiplied by
+// gelu'(Zp) if Zp is given (the backward pass; Zp may be Z: a thread reads a
+// value before it writes it).  Bound
 // by memory (V read, Vn written): 256 samples of width 64 in 38 us, 3.5 TB/s;
 // as two products and an activation pass 32 samples took 21 us.
 struct ZP {
     const float *W, *bias, *V, *Uh, *Gt;
     int T, TS, K2;
     float *Z, *Vn, *pool;
+    const float* Zp;
 };
 
 template <int C, bool TRW>
@@ -385,6 +457,13 @@ __global__ __launch_bounds__(256) void k_zlayer(ZP p)
 #pragma unroll
         for (int i = 0; i < 4; ++i) z[i] = acu[j][i] + (p.bias ? acc[j][i] + bc : acc[j][i]);
         const long at = ((long)b * C + c) * p.TS + t0 + w * 16 + 4 * g;
+        if (TRW && p.Zp) {
+            const float4 y = ld4(p.Zp + at);
+            z[0] *= gelu_d(y.x);
+            z[1] *= gelu_d(y.y);
+            z[2] *= gelu_d(y.z);
+            z[3] *= gelu_d(y.w);
+        }
         if (p.Z) *reinterpret_cast<float4*>(p.Z + at) = make_float4(z[0], z[1], z[2], z[3]);
         if (p.Vn)
             *reinterpret_cast<float4*>(p.Vn + at) = make_float4(gelu_f(z[0]), gelu_f(z[1]), gelu_f(z[2]), gelu_f(z[3]));

@@ -468,3 +468,62 @@ def test_fused_inference_matches_oracle_and_general_projection(B, d):
     gen = flat[1:1 + Y.numel()].cpu().numpy().reshape(65, d.O, d.T)
     assert rel(got, gen.astype(np.float64)) <= 1e-6
     assert float(flat[0]) == 0.0 and (flat[1 + Y.numel():] == 0.0).all()
+
+
+PLAIN4 = osno.Dims(four=(), C=64, T=256, K=16, L=2, H=64, O=32)
+
+
+@pytest.mark.parametrize("d,nb", [(FUSED[0], 33), (FUSED[1], 9), (FUSED[2], 1), (FUSED[3], 3), (PLAIN4, 5)],
+                         ids=["c32_33", "c64_9", "c64_o520_1", "c32_64_frequencies_3", "no_frequencies_5"])
+def test_fused_gradient_matches_oracle(B, d, nb):
+    """The fused backward pass at the edges of its tiles: one sample, more than
+    its chunks of 8 and 32, one layer, lift inputs of 4 and up to 516 channels
+    (one and several tiles, and the narrow product): every parameter block
+    against the oracle (the BF16 bar of this file)."""
+    import torch
+    rng = np.random.default_rng(50)
+    theta = (init(d, 51) + 0.05 * rng.standard_normal(osno.n_params(d))).astype(np.float32).astype(np.float64)
+    X = rng.uniform(-1, 1, (nb, 9))
+    Yt = rng.standard_normal((nb, d.O, d.T))
+    ref = osno.grad(theta, X, Yt, d)
+    s = make(B, d, theta)
+    g, loss = s.gradient(torch.tensor(X, dtype=torch.float32, device="cuda"),
+                         torch.tensor(Yt, dtype=torch.float32, device="cuda"))
+    g = g.cpu().numpy()
+    lref = osno.loss(theta, X, Yt, d)
+    assert abs(loss - lref) < 2e-2 * lref
+    o = 0
+    for name, sh in osno.param_shapes(d):
+        n = int(np.prod(sh))
+        e = rel(g[o:o + n], ref[o:o + n])
+        say(f"  grad {name}: rel-L2 {e:.2e}")
+        assert e < 2e-2, name
+        o += n
+
+
+def test_frame_gradient_over_several_segments(B):
+    """The transposed delays of a record longer than one staged segment (2048
+    samples), every parameter block against the oracle."""
+    import torch
+    d = osno.Dims(four=(3.0, 7.0, 9.0, 12.5, 14.0, 15.0), C=32, T=2048, K=8, L=1, H=32, O=16, frames=2)
+    rng = np.random.default_rng(52)
+    nb = 2
+    cells, shift, fr = frames_setup(d, rng, nb)
+    theta = (init_fr(d, 53) + 0.05 * rng.standard_normal(osno.n_params(d))).astype(np.float32).astype(np.float64)
+    off = [64.0, 64.0, 70.0] + [0.0] * 6
+    scl = [25.0] * 3 + [1000.0] * 6
+    X = np.concatenate([cells, rng.uniform(-1, 1, (nb, 6)) * 1000.0], 1)
+    src = (X - np.array(off)) / np.array(scl)
+    Yt = rng.standard_normal((nb, d.O, d.T))
+    ref = osno.grad(theta, src, Yt, d, shift=shift)
+    s = make_frames(B, d, theta, fr, off, scl)
+    g, _ = s.gradient(torch.tensor(X, dtype=torch.float32, device="cuda"),
+                      torch.tensor(Yt, dtype=torch.float32, device="cuda"))
+    g = g.cpu().numpy()
+    o = 0
+    for name, sh in osno.param_shapes(d):
+        n = int(np.prod(sh))
+        e = rel(g[o:o + n], ref[o:o + n])
+        say(f"  grad {name}: rel-L2 {e:.2e}")
+        assert e < 2e-2, name
+        o += n
