@@ -324,6 +324,12 @@ size_t state_bytes(const pstd3d_ctx* c, int n_shots)
     return spec_offset(fbytes) + (size_t)n_shots * c->g.sstride * sizeof(float2);
 }
 
+// device bytes of a context's model and shots, wherever they lie
+long touched_bytes(const pstd3d_ctx* c)
+{
+    return c->bytes + (c->visc ? 20L * c->g.n : 0L) + (long)c->n_shots * (c->g.fstride * 4 + c->g.sstride * 8);
+}
+
 int build_model(pstd3d_ctx* c, const pstd3d_model* m)
 {
     const int nx = c->nx, ny = c->ny, nz = c->nz;
@@ -981,6 +987,7 @@ int pstd3d_set_sources(pstd3d_ctx* c, int n_shots, const int32_t* shot_ofs, cons
         HIP_TRY(hipMalloc(&c->spec, sbytes));
     }
     c->n_shots = n_shots;
+    c->g.stream = touched_bytes(c) > STREAM_BYTES;
     HIP_TRY(hipMemset(c->fields, 0, fbytes));
     HIP_TRY(hipMemset(c->spec, 0, sbytes));
     if (!c->tuned) {
@@ -1051,10 +1058,13 @@ static int advance(pstd3d_ctx* const* ctxs, int n, int nt, float* const* traces,
 {
     std::vector<int> n0(n);
     bool prof = false;
+    long touched = 0;
     for (int i = 0; i < n; ++i) {
         n0[i] = (int)ctxs[i]->step;
         prof = prof || ctxs[i]->prof;
+        touched += touched_bytes(ctxs[i]);
     }
+    for (int i = 0; i < n; ++i) ctxs[i]->g.stream = touched > STREAM_BYTES;
     int done = 0;
     if (!prof && graphs_enabled() && nt >= 4) {
         std::vector<hipGraphExec_t> ex(n, nullptr);

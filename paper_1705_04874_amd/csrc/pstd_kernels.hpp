@@ -28,6 +28,7 @@ struct Geo {
     long fstride;                      // floats per shot of split fields (24 n)
     long sstride;                      // complex values per shot of spectra (18 nspec)
     int shot_fast;                     // update kernels' grid is (shots, row blocks)
+    int stream;                        // the update kernels pass the caches by (STREAM_BYTES)
 };
 
 // material coefficients pre-multiplied by dt (FP64 on the host, stored FP32)
@@ -286,14 +287,29 @@ __device__ __forceinline__ __attribute__((address_space(1))) char* scalar_base(T
     asm("" : "+s"(b));
     return b;
 }
+// STREAM: non-temporal (a run whose arrays together exceed the last-level cache
+// finds none of its split fields there a step later, and leaves more of it to
+// the spectra when they pass it by; the coefficients, which the shots of a
+// batch share, do not: 64 shots at 128^3 15.9 ms a step with them, 15.6 without).
+template <bool STREAM>
 __device__ __forceinline__ float ldf(const float* base, unsigned off)
 {
-    return *(const __attribute__((address_space(1))) float*)(scalar_base(base) + off);
+    const auto p = (const __attribute__((address_space(1))) float*)(scalar_base(base) + off);
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
 }
+template <bool STREAM>
 __device__ __forceinline__ void stf(float* base, unsigned off, float v)
 {
-    *(__attribute__((address_space(1))) float*)(scalar_base(base) + off) = v;
+    const auto p = (__attribute__((address_space(1))) float*)(scalar_base(base) + off);
+    if (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
+
+// Device bytes of the contexts that run together from which their update kernels
+// stream: the 256 MB of the last-level cache.  Microseconds per step without and with: 180 MB (96^3)
+// 154, 166; 225 MB 175, 184; 288 MB (120 x 96 x 120) 209, 204; 426 MB (128^3)
+// 275, 257; 665 MB (160 x 160 x 128) 416, 390; 3.4 GB (256^3) 2026, 1961.
+constexpr long STREAM_BYTES = 256L << 20;
 
 // Row r of a block's rows as the thread knows it: where a wave's 64 cells lie in
 // one row (NX a multiple of 64) it is made a scalar, and with it the row's y
@@ -336,7 +352,7 @@ constexpr int vel_waves()
 // ---------------------------------------------------------------------------
 // V phase tail: inverse x FFT of the 9 stress derivatives, velocity split-PML
 // update (eq. 2 second line), receivers vx vy vz, x FFT of the summed v.
-template <int NX, int NT>
+template <int NX, int NT, bool STREAM>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX, NT>()))) void k_vel(
     Geo g, Mat m, Pml pm, const float2* __restrict__ twx, float* __restrict__ fields, float2* __restrict__ spec,
     Rec rc, float* __restrict__ traces, const int* __restrict__ stepp, int* __restrict__ stepn, int n0, int ldt)
@@ -395,14 +411,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
         // outside the grid read valid ones and store nothing)
 #pragma unroll
         for (int comp = 0; comp < 3; ++comp) {
-            vp[i][3 * comp] = ldf(F + 3 * comp * g.n, cell[i]);
+            vp[i][3 * comp] = ldf<STREAM>(F + 3 * comp * g.n, cell[i]);
             vp[i][3 * comp + 1] = vp[i][3 * comp + 2] = 0.f;
-            dtr[i][comp] = ldf(m.dtr[comp], cell[i]);
+            dtr[i][comp] = ldf<false>(m.dtr[comp], cell[i]);
         }
         if (!in[i])
 #pragma unroll
             for (int q = 0; q < 9; ++q)
-                if (q % 3) vp[i][q] = ldf(F + q * g.n, cell[i]);
+                if (q % 3) vp[i][q] = ldf<STREAM>(F + q * g.n, cell[i]);
     }
 
     float vsum[CPT][3];
@@ -427,11 +443,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
         }
         if (ok[i]) {
 #pragma unroll
-            for (int q = 0; q < 9; q += 3) stf(F + q * g.n, cell[i], vp[i][q]);
+            for (int q = 0; q < 9; q += 3) stf<STREAM>(F + q * g.n, cell[i], vp[i][q]);
             if (!in[i])
 #pragma unroll
                 for (int q = 0; q < 9; ++q)
-                    if (q % 3) stf(F + q * g.n, cell[i], vp[i][q]);
+                    if (q % 3) stf<STREAM>(F + q * g.n, cell[i], vp[i][q]);
         }
     }
     __syncthreads();
@@ -477,7 +493,7 @@ __host__ __device__ constexpr bool first_part(int q) { return q < 9 ? q % 3 == 0
 // slot of velocity derivative q (order of e[] in k_str) among the nine stored ones
 __host__ __device__ constexpr int ep_slot(int q) { return q < 3 ? q : ((q - 3) ^ 1) + 3; }
 
-template <int NX, int NT, bool VISC = false>
+template <int NX, int NT, bool VISC, bool STREAM>
 __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* __restrict__ twx,
                                             float* __restrict__ fields, float2* __restrict__ spec,
                                             Rec rc, Inj inj, float* __restrict__ traces,
@@ -529,16 +545,16 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
         in[i] = undamped(pm, x, y, z);
         // an undamped cell reads only the first part of each component
 #pragma unroll
-        for (int q = 0; q < 15; ++q) sp[i][q] = first_part(q) ? ldf(F + q * g.n, cell) : 0.f;
+        for (int q = 0; q < 15; ++q) sp[i][q] = first_part(q) ? ldf<STREAM>(F + q * g.n, cell) : 0.f;
         if (!in[i])
 #pragma unroll
             for (int q = 0; q < 15; ++q)
-                if (!first_part(q)) sp[i][q] = ldf(F + q * g.n, cell);
-        mt[i][0] = ldf(m.dlam, cell);
-        mt[i][1] = ldf(m.dmu2, cell);
-        mt[i][2] = ldf(m.dmus[0], cell);
-        mt[i][3] = ldf(m.dmus[1], cell);
-        mt[i][4] = ldf(m.dmus[2], cell);
+                if (!first_part(q)) sp[i][q] = ldf<STREAM>(F + q * g.n, cell);
+        mt[i][0] = ldf<false>(m.dlam, cell);
+        mt[i][1] = ldf<false>(m.dmu2, cell);
+        mt[i][2] = ldf<false>(m.dmus[0], cell);
+        mt[i][3] = ldf<false>(m.dmus[1], cell);
+        mt[i][4] = ldf<false>(m.dmus[2], cell);
         const float bxi = pm.bi[0][x], bxh = pm.bh[0][x];
         const float byi = pm.bi[1][y], byh = pm.bh[1][y];
         const float bzi = pm.bi[2][z], bzh = pm.bh[2][z];
@@ -557,12 +573,12 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
         jr[i][1] = iptr[row0 + rr + 1];
         if constexpr (VISC) {
 #pragma unroll
-            for (int q = 0; q < 9; ++q) ep[i][q] = ldf(EP + ep_slot(q) * g.n, cell);
-            vm[i][0] = ldf(m.chi, cell);
-            vm[i][1] = ldf(m.eta2, cell);
-            vm[i][2] = ldf(m.etas[0], cell);
-            vm[i][3] = ldf(m.etas[1], cell);
-            vm[i][4] = ldf(m.etas[2], cell);
+            for (int q = 0; q < 9; ++q) ep[i][q] = ldf<STREAM>(EP + ep_slot(q) * g.n, cell);
+            vm[i][0] = ldf<false>(m.chi, cell);
+            vm[i][1] = ldf<false>(m.eta2, cell);
+            vm[i][2] = ldf<false>(m.etas[0], cell);
+            vm[i][3] = ldf<false>(m.etas[1], cell);
+            vm[i][4] = ldf<false>(m.etas[2], cell);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -621,7 +637,7 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
         if constexpr (VISC) {
             if (ok[i])
 #pragma unroll
-                for (int q = 0; q < 9; ++q) stf(EP + ep_slot(q) * g.n, cell, e[q]);
+                for (int q = 0; q < 9; ++q) stf<STREAM>(EP + ep_slot(q) * g.n, cell, e[q]);
         }
         // point sources: the entries of the wave's rows, 64 at a time, one load
         // per lane, then field by field through scalar registers.  (Read one by
@@ -664,11 +680,11 @@ __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* 
         if (ok[i]) {
 #pragma unroll
             for (int q = 0; q < 15; ++q)
-                if (first_part(q)) stf(F + q * g.n, cell, sp[i][q]);
+                if (first_part(q)) stf<STREAM>(F + q * g.n, cell, sp[i][q]);
             if (!in[i])
 #pragma unroll
                 for (int q = 0; q < 15; ++q)
-                    if (!first_part(q)) stf(F + q * g.n, cell, sp[i][q]);
+                    if (!first_part(q)) stf<STREAM>(F + q * g.n, cell, sp[i][q]);
         }
     }
     __syncthreads();

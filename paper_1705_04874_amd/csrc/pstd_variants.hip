@@ -58,17 +58,15 @@ struct LaunchX {
     static void vel(dim3 gr, hipStream_t st, Geo g, Mat m, Pml p, const float2* tw, float* f, float2* s, Rec r,
                     float* tr, const int* sp, int* sn, int n0, int ldt)
     {
-        hipLaunchKernelGGL((k_vel<N, T>), gr, dim3(T), 0, st, g, m, p, tw, f, s, r, tr, sp, sn, n0, ldt);
+        const auto fn = g.stream ? k_vel<N, T, true> : k_vel<N, T, false>;
+        hipLaunchKernelGGL(fn, gr, dim3(T), 0, st, g, m, p, tw, f, s, r, tr, sp, sn, n0, ldt);
     }
+    template <bool VISC>
     static void str(dim3 gr, hipStream_t st, Geo g, Mat m, Pml p, const float2* tw, float* f, float2* s, Rec r,
                     Inj in, float* tr, const int* sp, int n0, int ldt)
     {
-        hipLaunchKernelGGL((k_str<N, T>), gr, dim3(T), 0, st, g, m, p, tw, f, s, r, in, tr, sp, n0, ldt);
-    }
-    static void strv(dim3 gr, hipStream_t st, Geo g, Mat m, Pml p, const float2* tw, float* f, float2* s, Rec r,
-                     Inj in, float* tr, const int* sp, int n0, int ldt)
-    {
-        hipLaunchKernelGGL((k_str<N, T, true>), gr, dim3(T), 0, st, g, m, p, tw, f, s, r, in, tr, sp, n0, ldt);
+        const auto fn = g.stream ? k_str<N, T, VISC, true> : k_str<N, T, VISC, false>;
+        hipLaunchKernelGGL(fn, gr, dim3(T), 0, st, g, m, p, tw, f, s, r, in, tr, sp, n0, ldt);
     }
 };
 
@@ -79,7 +77,7 @@ void x_variants(VelVar* v, StrVar* s, int& n)
         constexpr int T = nt_candidate(N, I);
         if constexpr (T > 0) {
             v[n] = VelVar{LaunchX<N, T>::vel, T};
-            s[n] = StrVar{LaunchX<N, T>::str, LaunchX<N, T>::strv, T};
+            s[n] = StrVar{LaunchX<N, T>::template str<false>, LaunchX<N, T>::template str<true>, T};
             ++n;
         }
         x_variants<N, I + 1>(v, s, n);
