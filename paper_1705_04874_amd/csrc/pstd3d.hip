@@ -42,13 +42,14 @@ constexpr int ZF_VALUES[2] = {1, 6};
 
 // One spectrum between the z and the inverse y kernels: from input `in`, stored
 // in derivative slot `slot`, times the z symbol (zplus 0 / 1) or not (-1), and
-// the derivatives formed from it (the last one in its own slot)
+// the derivatives formed from it.  A single derivative's spectrum takes its
+// slot; that of two takes the place of its input (slot below 0)
 struct Der {
     int slot, axis, plus;   // axis 0, 1: the symbol that the y kernel applies; 2: none
 };
 void add_spectrum(PhaseDesc& p, int in, int zplus, std::initializer_list<Der> ders)
 {
-    const int slot = std::prev(ders.end())->slot;
+    const int slot = ders.size() == 1 ? ders.begin()->slot : p.in0 + in - 9;
     p.zslot[in][p.nz[in]] = slot;
     p.zplus[in][p.nz[in]++] = zplus;
     p.ysrc[p.nsrc] = slot;
@@ -57,6 +58,8 @@ void add_spectrum(PhaseDesc& p, int in, int zplus, std::initializer_list<Der> de
         p.yslot[p.nsrc][o] = d.slot;
         p.yaxis[p.nsrc][o] = d.axis;
         p.yplus[p.nsrc][o] = d.plus;
+        p.dsrc[p.nders] = p.nsrc;
+        p.dord[p.nders++] = o;
     }
     ++p.nsrc;
 }
@@ -83,6 +86,7 @@ PhaseDesc phase_s()
 {
     PhaseDesc p{};
     p.nin = 3;
+    p.in0 = 6;
     add_spectrum(p, 0, -1, {{3, 1, 1}, {0, 0, 0}});   // Dy+ vx, Dx- vx
     add_spectrum(p, 0, 1, {{5, 2, 0}});               // Dz+ vx
     add_spectrum(p, 1, -1, {{4, 0, 1}, {1, 1, 0}});   // Dx+ vy, Dy- vy
@@ -94,6 +98,17 @@ PhaseDesc phase_s()
 
 // spectra that the inverse y kernel reads, per phase (velocity, stress)
 constexpr int NSRC[2] = {8, 6};
+
+// Items of an inverse y launch: the phase's sources, or the nine derivatives one
+// by one where a block per source leaves YINV_SPLIT blocks or fewer (24 per
+// compute unit).  Microseconds per step by source and by derivative: 32^3 (512
+// blocks) 49.4, 45.5; 48^3 62.6, 60.7; 64^3 (1536) 73.8, 71.2; 128^3 (5120) 255,
+// 251; 32 shots at 32^3 (16384) 238, 240; 256^3 (18432) 1920, 1950.
+constexpr long YINV_SPLIT = 6144;
+int yinv_items(const Geo& g, int tyn, int shots, int phase)
+{
+    return (long)tyn * g.nz * shots * NSRC[phase] <= YINV_SPLIT ? 9 : NSRC[phase];
+}
 
 // non-finite check on sampled trace values: flag = 1 if any is not finite
 __global__ void k_check_finite(const float* __restrict__ tr, long n, int* __restrict__ flag)
@@ -583,7 +598,8 @@ void enqueue_step(pstd3d_ctx* c, hipStream_t st, float* traces, int n0, int ldt,
     c->zf.op(dim3(tzn, g.ny, S * ((6 + fpb - 1) / fpb)), st, g, c->twz, c->spec, 0, c->zdesc, 0, fpb);
     c->ev_end(e, st);
     e = c->ev_begin(PSTD_K_YINV_V, st);
-    c->yf.inv(dim3(tyn, g.nz, S * NSRC[0]), st, g, c->twy, c->spec, c->zdesc, 0, NSRC[0]);
+    const int items[2] = {yinv_items(g, tyn, S, 0), yinv_items(g, tyn, S, 1)};
+    c->yf.inv(dim3(tyn, g.nz, S * items[0]), st, g, c->twy, c->spec, c->zdesc, 0, items[0]);
     c->ev_end(e, st);
     e = c->ev_begin(PSTD_K_VEL, st);
     c->vel.fn(gx, st, g, c->M, c->P, c->twx, c->fields, c->spec, rec_of(c), traces, cur, nxt, n0, ldt);
@@ -596,7 +612,7 @@ void enqueue_step(pstd3d_ctx* c, hipStream_t st, float* traces, int n0, int ldt,
     c->zf.op(dim3(tzn, g.ny, S * ((3 + fpb - 1) / fpb)), st, g, c->twz, c->spec, 6, c->zdesc, 1, fpb);
     c->ev_end(e, st);
     e = c->ev_begin(PSTD_K_YINV_S, st);
-    c->yf.inv(dim3(tyn, g.nz, S * NSRC[1]), st, g, c->twy, c->spec, c->zdesc, 1, NSRC[1]);
+    c->yf.inv(dim3(tyn, g.nz, S * items[1]), st, g, c->twy, c->spec, c->zdesc, 1, items[1]);
     c->ev_end(e, st);
     e = c->ev_begin(PSTD_K_STR, st);
     c->str_fn(c->str)(gx, st, g, c->M, c->P, c->twx, c->fields, c->spec, rec_of(c), inj_of(c), traces, cur, n0,
@@ -672,7 +688,8 @@ int autotune(pstd3d_ctx* c)
             if (k == PSTD_TUNE_Y) {
                 const YFns v = c->yv[i];
                 const int tyn = (g.nxm + v.tile - 1) / v.tile + g.has_nyq;
-                e = timed([&] { v.inv(dim3(tyn, g.nz, S * NSRC[0]), nullptr, g, c->twy, c->spec, c->zdesc, 0, NSRC[0]); },
+                const int items = yinv_items(g, tyn, S, 0);
+                e = timed([&] { v.inv(dim3(tyn, g.nz, S * items), nullptr, g, c->twy, c->spec, c->zdesc, 0, items); },
                           &c->tune_us[k][i]);
             } else if (k == PSTD_TUNE_Z || k == PSTD_TUNE_ZT || k == PSTD_TUNE_ZF) {
                 // the velocity phase's z operator; the other two z knobs at
@@ -1245,7 +1262,8 @@ int pstd3d_derivs(pstd3d_ctx* c, int phase, const float* in_dev, float* out_dev,
     c->yf.fwd(dim3(tyn, g.nz, sd.nf), st, g, c->twy, c->spec, in0, sd.nf);
     c->zf.op(dim3(tzn, g.ny, (sd.nf + c->zfpb - 1) / c->zfpb), st, g, c->twz, c->spec, in0, c->zdesc, phase,
              c->zfpb);
-    c->yf.inv(dim3(tyn, g.nz, NSRC[phase]), st, g, c->twy, c->spec, c->zdesc, phase, NSRC[phase]);
+    const int items = yinv_items(g, tyn, 1, phase);
+    c->yf.inv(dim3(tyn, g.nz, items), st, g, c->twy, c->spec, c->zdesc, phase, items);
     c->xf.xinv(gx, st, g, c->twx, c->spec + 9 * g.nspec, out_dev);
     // the stress spectra are part of the state between steps: rebuild them
     enqueue_restore_spectra(c, st);

@@ -87,16 +87,17 @@ struct Inj {
 // kappa times the z symbol: 8 instead of 9 spectra in the velocity phase, 6
 // instead of 9 in the stress phase.
 struct PhaseDesc {
-    int nin;
+    int nin, in0;       // input spectra, the first one
     int nz[6];          // z kernel outputs of each input
-    int zslot[6][2];    // derivative slot each is stored in
+    int zslot[6][2];    // derivative slot each is stored in (below 0: its input's own spectrum)
     int zplus[6][2];    // -1: kappa alone, 0 / 1: times the D- / D+ z symbol
     int nsrc;           // spectra that the inverse y kernel reads
     int ysrc[8];        // their slots
-    int yn[8];          // derivatives formed from each (the last one in place)
+    int yn[8];          // derivatives formed from each (one: in place)
     int yslot[8][2];
     int yaxis[8][2];    // symbol applied: 0 x, 1 y, 2 none
     int yplus[8][2];    // 1: D+, 0: D-
+    int nders, dsrc[9], dord[9];   // the nine derivatives one by one: source and which of its derivatives
 };
 
 struct Ops {
@@ -119,7 +120,11 @@ struct ZDesc {
     Ops ops;
 };
 
-constexpr int rows_for(int nx) { return nx <= 32 ? 16 : nx <= 64 ? 8 : nx <= 160 ? 4 : 2; }
+// Rows per block of the update kernels.  Up to 32: 8 (16 left three quarters of
+// the chip without a block at 32^3: 50.8 us a step, 48.8 with 8); up to 48: 4
+// (48^3 65.8 with 8, 62.0); at 64 8 and 4 are even (64^3 72.9 and 71.7, 16 shots
+// of it 536 and 544).
+constexpr int rows_for(int nx) { return nx <= 32 ? 8 : nx <= 48 ? 4 : nx <= 64 ? 8 : nx <= 160 ? 4 : 2; }
 
 // Load through a pointer that addresses global memory.  Pointers read from a
 // device-resident descriptor are generic to the compiler, and a generic load
@@ -863,8 +868,11 @@ struct TileSym {
 // 550 and 517 us for 17 and 15 spectra read or written, against 511 and 523 for
 // 18 when the z kernel wrote all nine derivatives; the z kernel's part is
 // 515 -> 488 and 420 -> 298 us.
-// Every element is read before the first store, and the last derivative goes
-// back in place.  grid: (main tiles + Nyquist tile, nz, shots * nsrc).
+// A source of one derivative is transformed in place (every element is read
+// before the first store); one of two lies outside the derivatives' slots, so
+// that its derivatives can also be formed by two blocks (nsrc = 9: grid z runs
+// over the derivatives), which shortens the launch where the chip is not full.
+// grid: (main tiles + Nyquist tile, nz, shots * nsrc).
 template <int NY, int NT, int TX>
 __global__ __launch_bounds__(NT) void k_yinv(Geo g, const float2* __restrict__ twy, float2* spec,
                                              const ZDesc* __restrict__ zd, int phase, int nsrc)
@@ -877,7 +885,9 @@ __global__ __launch_bounds__(NT) void k_yinv(Geo g, const float2* __restrict__ t
     __shared__ float2 tw[NY];
     __shared__ float2 sy[SYL ? NY : 1];
     const PhaseDesc& ph = zd->ph[phase];
-    const int shot = blockIdx.z / nsrc, src = blockIdx.z % nsrc;
+    const bool single = nsrc == 9;   // a block per derivative
+    const int shot = blockIdx.z / nsrc, item = blockIdx.z % nsrc;
+    const int src = single ? ph.dsrc[item] : item;
     long off, cs, is;
     int ncol;
     if (!y_tile<NY, TX>(g, off, cs, is, ncol)) return;
@@ -889,8 +899,8 @@ __global__ __launch_bounds__(NT) void k_yinv(Geo g, const float2* __restrict__ t
     // x symbol of this thread's column (the Nyquist pencils: that of nx / 2)
     const int kx = cs == 1 ? blockIdx.x * TX + min((int)threadIdx.x % TX, ncol - 1) : g.nx / 2;
     const float2 sx = gld(zd->ops.sym[0][1] + kx);
-    const int n = ph.yn[src];
-    for (int o = 0; o < n; ++o) {
+    const int o0 = single ? ph.dord[item] : 0, o1 = single ? o0 + 1 : ph.yn[src];
+    for (int o = o0; o < o1; ++o) {
         // an offset the compiler cannot see through: without it the addresses
         // of every element are worked out before the loop and kept
         long zero = 0;
