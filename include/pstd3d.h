@@ -200,7 +200,8 @@ int pstd3d_profile_read(const pstd3d_ctx *c, int kind, double *total_ms, long *l
  *        not fit);
  *   PSTD_TUNE_VEL, PSTD_TUNE_STR  threads per block of the velocity and the
  *        stress update kernels (x transforms fused with the split-PML
- *        updates): 128, 256 or 512, at most the cells of a block;
+ *        updates): 128, 256 or 512, at most the cells of a block (of twice
+ *        its cells up to length 48);
  *   PSTD_TUNE_ZT  threads per block of the z kernels: 256, or 512 where the
  *        tile gives each of 512 threads a butterfly of a radix-8 (or 16) first
  *        pass (half the registers per thread, so twice the waves in flight);

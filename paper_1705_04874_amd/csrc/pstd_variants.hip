@@ -27,11 +27,15 @@ namespace {
 constexpr int N_TILES = 4;
 constexpr int TILE_CANDIDATES[N_TILES] = {8, 16, 32, 64};
 
-// threads per block of the update kernels of length N: 128, 256 and 512,
-// none above the cells of a block
+// Threads per block of the update kernels of length N: 128, 256 and 512, none
+// above the cells of a block; up to length 48, whose blocks were halved
+// (rows_for), none above the cells of twice the rows: a shape that a caller
+// measured and kept with the taller blocks can still be forced
+// (pstd3d_set_tuning).  There the largest count leaves up to half of its
+// threads without a cell.
 constexpr int nt_candidate(int n, int i)
 {
-    const int cells = rows_for(n) * n;
+    const int cells = (n <= 48 ? 2 : 1) * rows_for(n) * n;
     const int c[3] = {128, 256, 512};
     const int v = c[i];
     if (v > cells || v % 64 || v > 1024) return 0;

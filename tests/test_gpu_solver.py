@@ -574,3 +574,53 @@ def test_caller_workspace(B):
     np.testing.assert_array_equal(b.run(60).cpu().numpy(), ref)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("nx,counts", [(16, (128, 256)), (20, (128, 256)), (24, (128, 256)), (30, (128, 256)),
+                                       (32, (128, 256, 512)), (40, (128, 256)), (48, (128, 256))])
+def test_update_thread_counts_of_short_rows(B, nx, counts):
+    """Lengths up to 48 take update kernels of more threads than a block of
+    their rows has cells (128 to 256 cells): every count can be forced, and
+    three steps from a random state, with a smoothed source whose stencil wraps
+    around the grid's last row and a ragged last block (1200 rows by 8, 2250 by
+    8 and 4), agree with the FP64 oracle to this file's bar and with 128
+    threads to FP32 rounding (as every launch shape: 1e-5 of a field's largest
+    value)."""
+    shape = (30, 75, nx) if nx != 20 else (16, 75, nx)
+    nz, ny, _ = shape
+    rng = np.random.default_rng(60 + nx)
+    vp, vs, rho = hetero(shape, 61)
+    src = np.array([[nx - 1, ny - 1, nz - 1], [nx // 2, 30, 9]], np.int32)
+    rec = inputs.receiver_block(1, nx - 1, 3, ny - 3, 5)
+    w = inputs.Workload("short_rows", inputs.Model(vp, vs, rho), (10.0, 10.0, 10.0), 0.8e-3, 3, 4, 2.0, 1, 0.0, rec,
+                        src, np.stack([inputs.random_dc(rng, 1e6), inputs.random_dc(rng, 1e6)]),
+                        np.array([0, 2], np.int32), rng.standard_normal((2, 3)))
+    w.smooth = 1
+    amp = np.where(np.arange(24) < 9, 2e-7, 1.0)[:, None, None, None]
+    start = (amp * rng.standard_normal((24,) + shape)).astype(np.float32)
+    s = B.Solver.from_workload(w)
+    s.set_workload_sources(w)
+    s.set_state(start, 0)
+    start = s.get_state()   # the undamped cells' parts collapsed
+    o = oracle.Solver.from_workload(w)
+    o.set_sources(w.src_ijk, w.src_m, w.wavelet)
+    o.set_state(start.astype(np.float64))
+    o.step = 0
+    o.run(3)
+    ref = physics.collapse_undamped(o.get_state(), physics.undamped_mask(shape, *s.undamped_range()))
+    o.close()
+    got = {}
+    for nt in counts:
+        s.set_tuning(vel_threads=nt, str_threads=nt)
+        s.set_workload_sources(w)
+        t = s.tuning()
+        assert t["vel_threads"] == nt and t["str_threads"] == nt
+        s.set_state(start, 0)
+        say("short rows", nx, nt)
+        s.run(3)
+        got[nt] = s.get_state()
+        for name, ef, ep in physics.split_errors(got[nt], ref):
+            assert ef <= TOL and ep <= TOL, (nt, name, ef, ep)
+        scale = np.abs(got[128]).max(axis=(1, 2, 3))
+        assert (np.abs(got[nt] - got[128]).max(axis=(1, 2, 3)) <= 1e-5 * scale).all(), nt
+    s.close()
