@@ -1427,9 +1427,8 @@ struct sno {
           *part = nullptr, *lossd = nullptr, *phi = nullptr, *Xb = nullptr, *Yb = nullptr, *Y6 = nullptr,
           *dY6 = nullptr, *shift = nullptr, *Qm = nullptr, *dQm = nullptr, *bm = nullptr, *dbm = nullptr;
     int* idxd = nullptr;
-    // inference workspace of the fused path: trunk chunks of up to ibt
-    // samples, projection chunks of up to ibh
-    int ibt = 0, ibh = 0;
+    // inference workspace of the fused path (ensure_infer)
+    bool iready = false;
     float *iV[2] = {nullptr, nullptr}, *iVh = nullptr, *iUh = nullptr, *ipool = nullptr, *iQm = nullptr, *ibm = nullptr,
           *iY = nullptr, *ishift = nullptr;
     // partial sums of the split weight-gradient products
@@ -1459,7 +1458,7 @@ struct sno {
             (void)hipFree(*p);
             *p = nullptr;
         }
-        ibt = ibh = 0;
+        iready = false;
     }
     ~sno()
     {
@@ -1492,23 +1491,24 @@ struct sno {
         return PSTD_OK;
     }
 
-    // workspace of an inference over n samples (grown, never shrunk)
+    // workspace of an inference, for its largest chunks (IBT samples of the
+    // trunk, IBH of the projection; 0.4 GB at width 64, 1024 samples, 1024
+    // hidden and 2 x 256 output series) whatever the first call's n: later
+    // calls of more samples then neither allocate nor wait for the device, and
+    // can be captured into a graph
     static constexpr int IBT = 256, IBH = 64;
-    int ensure_infer(int n)
+    int ensure_infer()
     {
-        const int bt = std::min(n, IBT), bh = std::min(n, IBH);
-        if (bt <= ibt && bh <= ibh) return PSTD_OK;
-        free_iws();
+        if (iready) return PSTD_OK;
         const long C = cfg.C, T = cfg.T, K2 = 2 * cfg.K, FO = (long)F * O;
         auto al = [&](float** p, long m) { return hipMalloc(p, std::max<long>(m, 1) * sizeof(float)); };
-        if (al(&iV[0], bt * C * T) || al(&iV[1], bt * C * T) || al(&iVh, bt * C * K2) || al(&iUh, bt * C * K2) ||
-            al(&ipool, bt * (T / 64) * C) || al(&iQm, bh * ((FO + 15) / 16 * 16) * cfg.H) || al(&ibm, bh * FO) || al(&iY, bh * FO * T) ||
-            al(&ishift, (long)bh * F * cfg.n_rec)) {
+        if (al(&iV[0], IBT * C * T) || al(&iV[1], IBT * C * T) || al(&iVh, IBT * C * K2) || al(&iUh, IBT * C * K2) ||
+            al(&ipool, IBT * (T / 64) * C) || al(&iQm, IBH * ((FO + 15) / 16 * 16) * cfg.H) || al(&ibm, IBH * FO) ||
+            al(&iY, F == 2 ? IBH * FO * T : 0) || al(&ishift, (long)IBH * F * cfg.n_rec)) {
             free_iws();
             return sfail(PSTD_ENOMEM, "surrogate inference workspace");
         }
-        ibt = bt;
-        ibh = bh;
+        iready = true;
         return PSTD_OK;
     }
 };
@@ -1669,12 +1669,12 @@ void proj(sno* s, hipStream_t st, const snof::ProjP& p, int B)
 int infer(sno* s, hipStream_t st, const float* X, int n, float* Y, const float* scale, float* est)
 {
     const sno_cfg& c = s->cfg;
-    int rc = s->ensure_infer(n);
+    int rc = s->ensure_infer();
     if (rc) return rc;
     const int T = c.T, TS = T, H = c.H, O = s->O, FO = s->F * O;
     const float* th = s->theta;
-    for (int b0 = 0; b0 < n; b0 += s->ibt) {
-        const int B = std::min(s->ibt, n - b0);
+    for (int b0 = 0; b0 < n; b0 += sno::IBT) {
+        const int B = std::min<int>(sno::IBT, n - b0);
         const float* Xb = X + (long)b0 * 9;
         float *V[17], *Vh[16];
         for (int l = 0; l <= c.L; ++l) V[l] = s->iV[l & 1];
@@ -1683,8 +1683,8 @@ int infer(sno* s, hipStream_t st, const float* X, int n, float* Y, const float* 
         if (est)
             hipLaunchKernelGGL(k_head_tiles, dim3(B), dim3(64), 0, st, s->ipool, Xb, s->feat, s->dhead, c.C, T,
                                s->head_margin, est + b0);
-        for (int h0 = 0; h0 < B; h0 += s->ibh) {
-            const int Bh = std::min(s->ibh, B - h0);
+        for (int h0 = 0; h0 < B; h0 += sno::IBH) {
+            const int Bh = std::min<int>(sno::IBH, B - h0);
             const float* Xh = Xb + (long)h0 * 9;
             float* Yh = Y + (long)(b0 + h0) * O * T;
             snof::MixP mp{th + s->off_Q2, th + s->off_q2b, Xh, {}, Bh, FO, O, H, s->iQm, s->ibm};
@@ -2146,6 +2146,9 @@ int sno_train(sno* s, const float* X, const float* Y, int n, const sno_train_cfg
     const int B = std::min(tc->batch, n_fit);
     int rc = s->ensure(std::max(B, 32));
     if (rc) return rc;
+    // so that the predictions after a training find their workspace (if it does
+    // not fit now, the first of them says so)
+    if (s->fused && s->ensure_infer()) (void)hipGetLastError();
     // output normalisation: per-component RMS over the fitting samples
     double* ss = nullptr;
     S_TRY(hipMalloc(&ss, 4 * SQ_BLOCKS * sizeof(double)));

@@ -527,3 +527,55 @@ def test_frame_gradient_over_several_segments(B):
         say(f"  grad {name}: rel-L2 {e:.2e}")
         assert e < 2e-2, name
         o += n
+
+
+@pytest.mark.parametrize("first", ["predict", "train"])
+def test_predictions_allocate_once_and_can_be_captured(B, first):
+    """One prediction (or a training) allocates for good: predictions of more
+    samples take no device memory (their buffers at 300 samples are above
+    150 MB; 32 MB allow for the runtime's own) and one of them captured into a
+    graph gives the eager result on every replay, between eager calls."""
+    import torch
+    d = FULL_FR
+    rng = np.random.default_rng(60)
+    n = 300
+    cells, _, fr = frames_setup(d, rng, n)
+    theta = (init_fr(d, 61) + 0.02 * rng.standard_normal(osno.n_params(d))).astype(np.float32).astype(np.float64)
+    s = make_frames(B, d, theta, fr, [64.0, 64.0, 70.0] + [0.0] * 6, [25.0] * 3 + [1000.0] * 6)
+    X = torch.tensor(np.concatenate([cells, rng.uniform(-1, 1, (n, 6)) * 1000.0], 1), dtype=torch.float32,
+                     device="cuda")
+    Y = torch.zeros((n, 4, d.O // 4, d.T), dtype=torch.float32, device="cuda")
+    est = torch.zeros(n, dtype=torch.float32, device="cuda")
+
+    def predict(k, x=X):
+        assert B._L.sno_predict(s._h, B._dev(x), k, B._dev(Y), B._dev(est), B._stream_handle()) == 0
+
+    if first == "train":
+        s.train(X[:8], Y[:8], epochs=1, batch=4, lr=1e-3)
+    else:
+        predict(1)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for k in (10, 65, n):
+        predict(k)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 32 << 20
+    k = 100
+    say("captured prediction", first, k)
+    xs = X[:k].clone()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        predict(k, xs)
+    for r in range(3):
+        x = X[50 * r:50 * r + k].clone()
+        predict(k, x)
+        torch.cuda.synchronize()
+        want, we = Y[:k].clone(), est[:k].clone()
+        xs.copy_(x)
+        Y.zero_()
+        est.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y[:k], want) and torch.equal(est[:k], we), r
+        assert bool(want.any())
