@@ -1689,7 +1689,9 @@ int infer(sno* s, hipStream_t st, const float* X, int n, float* Y, const float* 
             float* Yh = Y + (long)(b0 + h0) * O * T;
             snof::MixP mp{th + s->off_Q2, th + s->off_q2b, Xh, {}, Bh, FO, O, H, s->iQm, s->ibm};
             for (int j = 0; j < 6; ++j) mp.inv[j] = s->feat.inv[3 + j];
-            hipLaunchKernelGGL(snof::k_qmix_frag, dim3(H / 32, (FO + 15) / 16), dim3(128), 0, st, mp);
+            // (a grid's y dimension ends at 65535: the kernel loops past it)
+            hipLaunchKernelGGL(snof::k_qmix_frag, dim3(H / 32, std::min((FO + 15) / 16, 65535)), dim3(128), 0, st,
+                               mp);
             snof::ProjP pp{V[c.L] + (long)h0 * c.C * TS, th + s->off_Q1, th + s->off_q1b, s->iQm, s->ibm,
                            s->F == 1 ? scale : nullptr, T, TS, H, FO, c.n_rec, 0, 0, 0, s->F == 1 ? Yh : s->iY};
             proj(s, st, pp, Bh);

@@ -499,34 +499,36 @@ struct MixP {
 __global__ __launch_bounds__(128) void k_qmix_frag(MixP p)
 {
     const int tid = threadIdx.x, lane = tid & 63, half = tid >> 6, r = lane & 15, g = lane >> 4;
-    const int s = blockIdx.x, o16 = blockIdx.y, n16 = gridDim.y;
-    const int fo = o16 * 16 + r, fc = min(fo, p.FO - 1);   // rows past FO repeat the last one
-    const int fr = fc / p.O, o = fc - fr * p.O;
+    const int s = blockIdx.x, n16 = (p.FO + 15) / 16;
     const int h = s * 32 + g * 8 + half * 4;
-    float4 q[6];
-    float qb[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        const long row = (long)(fr * 6 + j) * p.O + o;
-        q[j] = ld4(p.Q2 + row * p.H + h);
-        qb[j] = p.q2b[row];
-    }
-    const long slot = (((long)s * n16 + o16) * 2 + half) * 256 + lane * 4;
     const long per = (long)n16 * 16 * p.H;
-    for (int b = 0; b < p.B; ++b) {
-        float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-        float ab = 0.f;
+    for (int o16 = blockIdx.y; o16 < n16; o16 += gridDim.y) {
+        const int fo = o16 * 16 + r, fc = min(fo, p.FO - 1);   // rows past FO repeat the last one
+        const int fr = fc / p.O, o = fc - fr * p.O;
+        float4 q[6];
+        float qb[6];
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
-            const float m = p.X[b * 9 + 3 + j] * p.inv[j];
-            a.x += m * q[j].x;
-            a.y += m * q[j].y;
-            a.z += m * q[j].z;
-            a.w += m * q[j].w;
-            ab += m * qb[j];
+            const long row = (long)(fr * 6 + j) * p.O + o;
+            q[j] = ld4(p.Q2 + row * p.H + h);
+            qb[j] = p.q2b[row];
         }
-        *reinterpret_cast<float4*>(p.Qm + b * per + slot) = a;
-        if (s == 0 && tid < 16 && fo < p.FO) p.bm[(long)b * p.FO + fo] = ab;
+        const long slot = (((long)s * n16 + o16) * 2 + half) * 256 + lane * 4;
+        for (int b = 0; b < p.B; ++b) {
+            float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+            float ab = 0.f;
+#pragma unroll
+            for (int j = 0; j < 6; ++j) {
+                const float m = p.X[b * 9 + 3 + j] * p.inv[j];
+                a.x += m * q[j].x;
+                a.y += m * q[j].y;
+                a.z += m * q[j].z;
+                a.w += m * q[j].w;
+                ab += m * qb[j];
+            }
+            *reinterpret_cast<float4*>(p.Qm + b * per + slot) = a;
+            if (s == 0 && tid < 16 && fo < p.FO) p.bm[(long)b * p.FO + fo] = ab;
+        }
     }
 }
 

@@ -579,3 +579,40 @@ def test_predictions_allocate_once_and_can_be_captured(B, first):
         torch.cuda.synchronize()
         assert torch.equal(Y[:k], want) and torch.equal(est[:k], we), r
         assert bool(want.any())
+
+
+def test_prediction_of_more_output_tiles_than_a_grid_dimension(B):
+    """131 080 receivers with two frames are 65 540 tiles of 16 output series,
+    past the 65 535 blocks of a grid's y dimension: the series of eight
+    receivers from the first to the last equal those of a network of just these
+    receivers (the same weights, products and sums in another tiling: 1e-6)."""
+    import torch
+    n_rec, T, C, K, H = 131080, 128, 32, 8, 32
+    pick = np.array([0, 1, 65539, 65540, 131069, 131070, 131072, 131079])
+    assert 4 * n_rec + 3 * n_rec + pick[4] >= 16 * 65535   # the last receivers' vz in the second frame
+    rng = np.random.default_rng(62)
+    four = (3.0, 7.0, 9.0, 12.5, 14.0, 15.0)
+    d = osno.Dims(four=four, C=C, T=T, K=K, L=1, H=H, O=4 * pick.size, frames=2)
+    small = (init_fr(d, 63) + 0.02 * rng.standard_normal(osno.n_params(d))).astype(np.float32)
+    nq2 = 2 * 6 * d.O
+    head, q2, q2b = small[:-nq2 * (H + 1)], small[-nq2 * (H + 1):-nq2], small[-nq2:]
+    # rows (frame, moment component, wave component, receiver)
+    big2 = np.full((48, n_rec, H), 0.01, np.float32)
+    big2[:, pick] = q2.reshape(48, pick.size, H)
+    bigb = np.full((48, n_rec), 0.01, np.float32)
+    bigb[:, pick] = q2b.reshape(48, pick.size)
+    rec = np.stack([32 + np.arange(n_rec) % 64, 32 + np.arange(n_rec) // 64 % 64, np.full(n_rec, 20)], 1).astype(np.int32)
+    cells, _, fr = frames_setup(d, rng, 2)
+    off, scl = [64.0, 64.0, 70.0] + [0.0] * 6, [25.0] * 3 + [1000.0] * 6
+    X = torch.tensor(np.concatenate([cells, rng.uniform(-1, 1, (2, 6)) * 1000.0], 1), dtype=torch.float32, device="cuda")
+    out = {}
+    for name, r, th in (("small", rec[pick], small), ("big", rec, np.concatenate([head, big2.ravel(), bigb.ravel()]))):
+        say("tiles", name, len(r))
+        s = B.Surrogate(len(r), T, C, K, 1, H, off, scl, th, four_cycles=four, frames=dict(fr, rec_ijk=r))
+        Y, _ = s.predict(X)
+        out[name] = (Y if name == "small" else Y[:, :, torch.from_numpy(pick).cuda()]).cpu().numpy().astype(np.float64)
+        del Y
+        s.close()
+    torch.cuda.empty_cache()
+    for k in range(pick.size):
+        assert rel(out["big"][:, :, k], out["small"][:, :, k]) <= 1e-6, pick[k]
