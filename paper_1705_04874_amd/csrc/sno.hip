@@ -65,7 +65,8 @@ __global__ void k_gelu(const float* __restrict__ z, float* __restrict__ y, long 
         y[i] = gelu_f(z[i]);
 }
 
-__global__ void k_gelu_bwd(const float* __restrict__ dy, const float* __restrict__ z, float* __restrict__ dz, long n)
+// (dz may be dy)
+__global__ void k_gelu_bwd(const float* dy, const float* __restrict__ z, float* dz, long n)
 {
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
         dz[i] = dy[i] * gelu_d(z[i]);

@@ -616,3 +616,27 @@ def test_prediction_of_more_output_tiles_than_a_grid_dimension(B):
     torch.cuda.empty_cache()
     for k in range(pick.size):
         assert rel(out["big"][:, :, k], out["small"][:, :, k]) <= 1e-6, pick[k]
+
+
+def test_gradient_of_sixteen_hidden_rows_matches_oracle(B):
+    """The smallest hidden width: its products have no activation epilogue, and
+    the gradient to the hidden rows is multiplied by the activation's
+    derivative in place, in a pass of its own (the BF16 bar of this file)."""
+    import torch
+    d = osno.Dims(four=(3.0, 7.0, 12.5), C=16, T=64, K=4, L=2, H=16, O=8)
+    rng = np.random.default_rng(64)
+    theta = (init(d, 65) + 0.05 * rng.standard_normal(osno.n_params(d))).astype(np.float32).astype(np.float64)
+    X = rng.uniform(-1, 1, (4, 9))
+    Yt = rng.standard_normal((4, d.O, d.T))
+    ref = osno.grad(theta, X, Yt, d)
+    s = make(B, d, theta)
+    g, _ = s.gradient(torch.tensor(X, dtype=torch.float32, device="cuda"),
+                      torch.tensor(Yt, dtype=torch.float32, device="cuda"))
+    g = g.cpu().numpy()
+    o = 0
+    for name, sh in osno.param_shapes(d):
+        n = int(np.prod(sh))
+        e = rel(g[o:o + n], ref[o:o + n])
+        say(f"  grad {name}: rel-L2 {e:.2e}")
+        assert e < 2e-2, name
+        o += n
