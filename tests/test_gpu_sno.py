@@ -640,3 +640,65 @@ def test_gradient_of_sixteen_hidden_rows_matches_oracle(B):
         say(f"  grad {name}: rel-L2 {e:.2e}")
         assert e < 2e-2, name
         o += n
+
+
+@pytest.mark.parametrize("d,nb", [
+    (osno.Dims(four=inputs.sno_fourier_cycles(16, 2.0, 40.0), pos_mod=True, C=64, T=256, K=16, L=2, H=48, O=64), 9),
+    (osno.Dims(four=inputs.sno_fourier_cycles(16, 2.0, 40.0), C=32, T=512, K=12, L=3, H=80, O=48, frames=2), 3),
+    (osno.Dims(four=(), C=32, T=128, K=8, L=1, H=48, O=36), 33),
+    (osno.Dims(four=(3.0, 7.0, 9.0, 12.5, 14.0, 15.0), C=64, T=1024, K=14, L=4, H=112, O=32, frames=2), 2)],
+    ids=["c64_k16", "c32_k12_frames", "c32_no_frequencies", "c64_k14_frames"])
+def test_fused_and_general_path_agree_bit_for_bit(B, d, nb):
+    """A hidden width that is no multiple of 32 takes the general path
+    throughout; the same network with 16 more hidden rows, to which the output
+    projection gives weight zero, takes the fused kernels.  Both form the same
+    products of the same rounded operands in the same order (the added rows
+    contribute exact zeros), so outputs, loss and every gradient block are the
+    same bit for bit."""
+    import dataclasses
+    import torch
+    rng = np.random.default_rng(70)
+    wide = dataclasses.replace(d, H=d.H + 16)
+    theta = (init_fr(d, 71) + 0.05 * rng.standard_normal(osno.n_params(d))).astype(np.float32)
+
+    def blocks(dim, flat):
+        out, o = {}, 0
+        for name, sh in osno.param_shapes(dim):
+            n = int(np.prod(sh))
+            out[name] = flat[o:o + n].reshape(sh)
+            o += n
+        return out
+
+    p = blocks(d, theta)
+    q = dict(p)
+    q["Q1"] = np.concatenate([p["Q1"], 0.1 * rng.standard_normal((16, d.C)).astype(np.float32)])
+    q["q1b"] = np.concatenate([p["q1b"], np.full(16, 0.2, np.float32)])
+    q["Q2"] = np.concatenate([p["Q2"], np.zeros((p["Q2"].shape[0], 16), np.float32)], axis=1)
+    padded = np.concatenate([q[name].ravel() for name, _ in osno.param_shapes(wide)])
+    if d.frames == 2:
+        cells, _, fr = frames_setup(d, rng, nb)
+        off, scl = [64.0, 64.0, 70.0] + [0.0] * 6, [25.0] * 3 + [1000.0] * 6
+        X = np.concatenate([cells, rng.uniform(-1, 1, (nb, 6)) * 1000.0], 1)
+        nets = [make_frames(B, dim, th, fr, off, scl) for dim, th in ((d, theta), (wide, padded))]
+    else:
+        X = rng.uniform(-1, 1, (nb, 9))
+        nets = [make(B, dim, th) for dim, th in ((d, theta), (wide, padded))]
+    Xd = torch.tensor(X, dtype=torch.float32, device="cuda")
+    Yt = torch.tensor(rng.standard_normal((nb, d.O, d.T)), dtype=torch.float32, device="cuda")
+    out, grad, loss = [], [], []
+    for s, dim in zip(nets, (d, wide)):
+        say("both paths", dim.H)
+        out.append((s.forward(Xd).cpu().numpy(), s.predict(Xd)[0].cpu().numpy()))
+        g, ls = s.gradient(Xd, Yt)
+        grad.append(blocks(dim, g.cpu().numpy()))
+        loss.append(ls)
+        s.close()
+    assert np.abs(out[0][0]).max() > 0
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+    assert loss[0] == loss[1]
+    for name, _ in osno.param_shapes(d):
+        a, b = grad[0][name], grad[1][name]
+        b = b[:, :d.H] if name == "Q2" else b[:d.H] if name in ("Q1", "q1b") else b
+        assert np.abs(a).max() > 0, name
+        np.testing.assert_array_equal(a, b, err_msg=name)
