@@ -327,3 +327,56 @@ def test_layered384_multistep_against_stored_oracle_planes(B):
                 worst_part = max(worst_part, ep)
                 assert ep <= 1e-4, (name, oracle.STATE_NAMES[f], ep)
         say(f"  plane {name}: worst field rel-L2 {worst_field:.2e}, worst split part {worst_part:.2e}")
+
+
+@pytest.mark.parametrize("ny", [16, 75, 144, 240, 384])
+def test_derivatives_formed_in_turn_equal_those_of_single_blocks(B, ny):
+    """The inverse y kernel gives each derivative a block of its own where the
+    launch is small, and otherwise one block per spectrum, which forms both
+    derivatives of a spectrum in turn from its tile (at 240 the widest tile
+    leaves no room for the symbol in LDS).  A batch of shots takes the second
+    form, one shot the first: with every built y tile, two steps of a batch
+    from one random state per chosen shot equal those of the shot alone, every
+    split part, to FP32 rounding (1e-5 of its largest value, as for every launch
+    shape).  The single blocks are checked against the oracle above."""
+    import re
+    src = open(os.path.join(ROOT, "paper_1705_04874_amd", "csrc", "pstd3d.hip")).read()
+    split = int(re.search(r"YINV_SPLIT = (\d+);", src).group(1))
+    h, dt, nz = (10.0, 12.0, 9.0), 0.8e-3, 16
+    rng = np.random.default_rng(9)
+    for nx in (20, 75):
+        shape = (nz, ny, nx)
+        vp = 2500 + 500 * rng.random(shape)
+        args = (vp, vp / 1.8, 310 * vp ** 0.25, h, dt)
+        amp = np.where(np.arange(24) < 9, 2e-7, 1.0)[:, None, None, None]
+        st = (amp * rng.standard_normal((24,) + shape)).astype(np.float32)
+        none = (np.zeros((0, 3)), np.zeros((0, 6)), np.zeros((0, 1)))
+        one = B.Solver(*args, pml=4, kspace=1)
+        one.set_sources([0, 0], *none)
+        batch = B.Solver(*args, pml=4, kspace=1)
+        tiles = list(one.tuning()["y_tile_candidates"])
+        count = {t: -(-((nx + 1) // 2) // t) + (nx % 2 == 0) for t in tiles}
+        shots = split // (6 * nz * min(count.values())) + 1
+        for tile in tiles:
+            # six spectra in the stress phase, eight in the velocity phase
+            assert count[tile] * nz * 8 <= split < count[tile] * nz * 6 * shots
+            kw = dict(one.tuning_values(), y_tile=tile)
+            one.set_tuning(**kw)
+            batch.set_tuning(**kw)
+            one.set_sources([0, 0], *none)
+            batch.set_sources([0] * (shots + 1), *none)
+            one.set_state(st, 0)
+            one.run(2)
+            ref = one.get_state()
+            scale = np.abs(ref).max(axis=(1, 2, 3))
+            assert (scale > 0).all()
+            chosen = (0, shots // 2, shots - 1)
+            for k in chosen:
+                batch.set_state(st, 0, shot=k)
+            say("in turn", nx, ny, tile, shots)
+            batch.run(2)
+            for k in chosen:
+                err = np.abs(batch.get_state(k) - ref).max(axis=(1, 2, 3))
+                assert (err <= 1e-5 * scale).all(), (nx, tile, k, (err / scale).max())
+        one.close()
+        batch.close()
