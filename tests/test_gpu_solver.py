@@ -624,3 +624,53 @@ def test_update_thread_counts_of_short_rows(B, nx, counts):
         scale = np.abs(got[128]).max(axis=(1, 2, 3))
         assert (np.abs(got[nt] - got[128]).max(axis=(1, 2, 3)) <= 1e-5 * scale).all(), nt
     s.close()
+
+
+@pytest.mark.parametrize("shape", [(30, 24, 40), (20, 24, 75)])
+def test_viscous_update_that_streams(B, shape):
+    """Where the contexts that run together hold more than the last-level cache
+    (256 MB) their update kernels pass it by.  A small viscous model beside a
+    128^3 one takes that form of the viscous stress update: traces and all 33
+    state fields against the oracle (this file's bar) and against the model
+    alone, with every thread count of the update kernels, to FP32 rounding
+    (1e-5 of a field's largest value, as for every launch shape)."""
+    nt = 60
+    w = small_workload(shape=shape, nt=nt, shots=1, seed=22)
+    rng = np.random.default_rng(122)
+    w.chi = 2.0e5 + 3.0e5 * rng.random(shape)
+    w.eta = 1.5e5 + 2.5e5 * rng.random(shape)
+    w.eta[:5] = 0.0
+    o = oracle.Solver.from_workload(w)
+    o.set_sources(w.src_ijk, w.src_m, w.wavelet)
+    otr = o.run(nt)
+    ref = o.get_state()
+    o.close()
+    big_w = inputs.layered128_shots(1, nt=nt)
+    big = B.Solver.from_workload(big_w)
+    big.set_workload_sources(big_w)
+    assert big.workspace_size(1) > 256 << 20
+    s = B.Solver.from_workload(w)
+    s.set_workload_sources(w)
+    assert s.n_state == 33 and s.workspace_size(1) < 128 << 20
+    ref = physics.collapse_undamped(ref, physics.undamped_mask(shape, *s.undamped_range()))
+    base = s.tuning_values()
+    for n in s.tuning()["str_threads_candidates"]:
+        s.set_tuning(**dict(base, vel_threads=n, str_threads=n))
+        s.reset()
+        alone, st0 = s.run(nt).cpu().numpy(), s.get_state()
+        s.reset()
+        big.reset()
+        say("viscous beside a large model", shape, n)
+        traces = B.run_many([s, big], nt)[0].cpu().numpy()
+        st = s.get_state()
+        for c in range(4):
+            assert rel(traces[0, c], otr[c]) <= TOL, (n, c)
+        for name, ef, ep in physics.split_errors(st, ref):
+            assert ef <= TOL and ep <= TOL, (n, name, ef, ep)
+        for f in range(24, 33):
+            assert rel(st[f], ref[f]) <= TOL, (n, f)
+        for a, b in ((traces[0], alone[0]), (st, st0)):
+            ax = tuple(range(1, a.ndim))
+            assert (np.abs(a - b).max(axis=ax) <= 1e-5 * np.abs(b).max(axis=ax)).all(), n
+    s.close()
+    big.close()
