@@ -482,15 +482,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(vel_waves<NX
 }
 
 // ---------------------------------------------------------------------------
-// S phase tail: inverse x FFT of the 9 velocity derivatives, stress split-PML
-// update (eq. 2 first line), source injection, receiver p (eq. 3), x FFT of
-// the 6 summed stresses.  Bound by memory where the grid is large and by the
-// vector pipe below: at 384 x 384 x 256 it moves 5.2 GB in 1.25 ms, and of its
-// instructions more than a third were addresses (2691 vector instructions per
-// thread at 384 with 64-bit indices, a division per cell and a branch per
-// element of the loads, 2120 without the injection loop now).  Velocity and
-// stress update together at 128^3: 158 -> 137 us; with a smoothed source at
-// 125 x 75 x 300 the stress update went from 207 to 100 us.
 // the first split part of a stress component (parts 0-8: three per normal
 // component, 9-14: two per shear component)
 __host__ __device__ constexpr bool first_part(int q) { return q < 9 ? q % 3 == 0 : (q - 9) % 2 == 0; }
@@ -498,6 +489,16 @@ __host__ __device__ constexpr bool first_part(int q) { return q < 9 ? q % 3 == 0
 // slot of velocity derivative q (order of e[] in k_str) among the nine stored ones
 __host__ __device__ constexpr int ep_slot(int q) { return q < 3 ? q : ((q - 3) ^ 1) + 3; }
 
+// S phase tail: inverse x FFT of the 9 velocity derivatives, stress split-PML
+// update (eq. 2 first line), source injection, receiver p (eq. 3), x FFT of
+// the 6 summed stresses.  Bound by memory where the grid is large and by the
+// vector pipe below: at 384 x 384 x 256 it moves 5.88 GB (5.74 without the
+// lines fetched whole at the ends of the rows) in 1.23 ms, 4.8 TB/s, and of its
+// instructions more than a third were addresses (2691 vector instructions per
+// thread at 384 with 64-bit indices, a division per cell and a branch per
+// element of the loads, 2120 without the injection loop now).  Velocity and
+// stress update together at 128^3: 158 -> 137 us (126 since they stream); with a
+// smoothed source at 125 x 75 x 300 the stress update went from 207 to 100 us.
 template <int NX, int NT, bool VISC, bool STREAM>
 __global__ __launch_bounds__(NT) void k_str(Geo g, Mat m, Pml pm, const float2* __restrict__ twx,
                                             float* __restrict__ fields, float2* __restrict__ spec,

@@ -1,4 +1,4 @@
-// Variants of one group of grid lengths (PSTD_GROUP, 0 .. PSTD_GROUPS - 1):
+// Variants of one group of grid lengths (PSTD_GROUP, 0 .. 7):
 // compiled once per group.  All lengths factor into 2, 3 and 5.
 #include "pstd_variants.hpp"
 

@@ -55,7 +55,6 @@ struct Variants {
 };
 
 // the groups' tables (false: length not in the group)
-constexpr int PSTD_GROUPS = 8;
 bool variants_0(int n, Variants* v);
 bool variants_1(int n, Variants* v);
 bool variants_2(int n, Variants* v);

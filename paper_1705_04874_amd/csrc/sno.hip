@@ -1482,7 +1482,7 @@ struct sno {
             al(&shift, (long)B * F * cfg.n_rec) || al(&Qm, (long)B * F * O * H) || al(&dQm, (long)B * F * O * H) ||
             al(&bm, (long)B * F * O) || al(&dbm, (long)B * F * O) || al(&Vb, L * B * C * T) || al(&Vh, L * B * C * K2) || al(&Z, L * B * C * T) ||
             al(&Uh, (long)B * C * K2) || al(&Hp, (long)B * H * T) || al(&Hq, (long)B * H * T) ||
-            al(&Y, (long)B * O * T) || al(&X0, (long)B * std::max(C, (long)O) * T) || al(&X1, (long)B * C * T) ||
+            al(&Y, (long)B * O * T) || al(&X0, (long)B * C * T) || al(&X1, (long)B * C * T) ||
             al(&X2, (long)B * C * T) || al(&dH, (long)B * H * T) || al(&dUh, (long)B * C * K2) ||
             al(&dVh, (long)B * C * K2) || al(&part, (long)B * O) || al(&lossd, 4) || al(&phi, (long)B * (C + 7)) ||
             al(&Xb, (long)B * 9) || al(&Yb, (long)B * O * T) || al(&kws, kws_all) || al(&wb, (long)B * 4) ||

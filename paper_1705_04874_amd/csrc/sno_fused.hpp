@@ -2,8 +2,9 @@
 // 64, up to 16 modes).  They form the same products in the same order as the
 // general GEMM path of sno.hip (BF16 operands rounded where they are staged,
 // one chain of 16x16x32 MFMA over ascending k per output, FP32 in memory), so
-// the outputs agree bit for bit up to the last FP32 sums; what they save is
-// passes over memory, launches and idle compute units.
+// outputs and gradients agree with it bit for bit (the error estimates' sums
+// over time run in another order); what they save is passes over memory,
+// launches and idle compute units.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -47,7 +48,8 @@ struct LiftP {
     float* Aout;         // [B][NA][TS] or null
     float* V;            // [B][C][TS]
 };
-constexpr int LIFT_TAB = 130, LIFT_NA = 544;   // rows and channels at 64 frequencies
+constexpr int LIFT_NA = 544;   // channels at SNO_MAX_FOUR frequencies with position products, in whole slices of 32
+static_assert(LIFT_NA >= (4 + 8 * SNO_MAX_FOUR + 31) / 32 * 32, "the channels' rows and factors fit LDS");
 
 template <int C>
 __global__ __launch_bounds__(256) void k_lift(LiftP p)
