@@ -1428,10 +1428,7 @@ struct sno {
           *part = nullptr, *lossd = nullptr, *phi = nullptr, *Xb = nullptr, *Yb = nullptr, *Y6 = nullptr,
           *dY6 = nullptr, *shift = nullptr, *Qm = nullptr, *dQm = nullptr, *bm = nullptr, *dbm = nullptr;
     int* idxd = nullptr;
-    // inference workspace of the fused path (ensure_infer)
-    bool iready = false;
-    float *iV[2] = {nullptr, nullptr}, *iVh = nullptr, *iUh = nullptr, *ipool = nullptr, *iQm = nullptr, *ibm = nullptr,
-          *iY = nullptr, *ishift = nullptr;
+    float* iws = nullptr;      // inference workspace of the fused path (ensure_infer)
     // partial sums of the split weight-gradient products
     static constexpr long kws_n = 4L << 20;    // of one product
     static constexpr long kws_all = 8L << 20;   // of products that go out together
@@ -1453,19 +1450,10 @@ struct sno {
         idxd = nullptr;
         bmax = 0;
     }
-    void free_iws()
-    {
-        for (float** p : {&iV[0], &iV[1], &iVh, &iUh, &ipool, &iQm, &ibm, &iY, &ishift}) {
-            (void)hipFree(*p);
-            *p = nullptr;
-        }
-        iready = false;
-    }
     ~sno()
     {
         free_ws();
-        free_iws();
-        for (float* p : {theta, grad, m1, m2, Fb, G, Ft, Gt, lift_tab, dscale, dhead}) (void)hipFree(p);
+        for (float* p : {theta, grad, m1, m2, Fb, G, Ft, Gt, lift_tab, dscale, dhead, iws}) (void)hipFree(p);
         (void)hipFree(lift_meta);
         (void)hipFree(drec);
         (void)hipFree(dcum);
@@ -1492,24 +1480,45 @@ struct sno {
         return PSTD_OK;
     }
 
-    // workspace of an inference, for its largest chunks (IBT samples of the
-    // trunk, IBH of the projection; 0.4 GB at width 64, 1024 samples, 1024
-    // hidden and 2 x 256 output series) whatever the first call's n: later
-    // calls of more samples then neither allocate nor wait for the device, and
-    // can be captured into a graph
+    // Buffers of an inference in chunks of bt samples of the trunk and bh of the
+    // projection, one after the other from base on (null: sizes only); returns
+    // the floats they take
+    struct InferWs {
+        float *V[2], *Vh, *Uh, *pool, *Qm, *bm, *Y, *shift;
+    };
+    long infer_ws(float* base, long bt, long bh, InferWs& w) const
+    {
+        const long C = cfg.C, T = cfg.T, K2 = 2 * cfg.K, FO = (long)F * O;
+        long at = 0;
+        auto take = [&](float** p, long m) {
+            *p = base ? base + at : nullptr;
+            at += (m + 63) / 64 * 64;
+        };
+        take(&w.V[0], bt * C * T);
+        take(&w.V[1], bt * C * T);
+        take(&w.Vh, bt * C * K2);
+        take(&w.Uh, bt * C * K2);
+        take(&w.pool, bt * (T / 64) * C);
+        take(&w.Qm, bh * ((FO + 15) / 16 * 16) * cfg.H);
+        take(&w.bm, bh * FO);
+        take(&w.Y, F == 2 ? bh * FO * T : 0);
+        take(&w.shift, bh * F * cfg.n_rec);
+        return at;
+    }
+    // Its memory, for the largest chunks (IBT and IBH samples; 0.4 GB at width
+    // 64, 1024 samples, 1024 hidden and 2 x 256 output series) whatever the first
+    // call's n: later calls of more samples then neither allocate nor wait for
+    // the device, and can be captured into a graph.  A call packs its buffers for
+    // its own n, so that a small one touches few pages (one source 122.0 us, and
+    // 123.5 with each buffer at its place for the largest chunks).
     static constexpr int IBT = 256, IBH = 64;
     int ensure_infer()
     {
-        if (iready) return PSTD_OK;
-        const long C = cfg.C, T = cfg.T, K2 = 2 * cfg.K, FO = (long)F * O;
-        auto al = [&](float** p, long m) { return hipMalloc(p, std::max<long>(m, 1) * sizeof(float)); };
-        if (al(&iV[0], IBT * C * T) || al(&iV[1], IBT * C * T) || al(&iVh, IBT * C * K2) || al(&iUh, IBT * C * K2) ||
-            al(&ipool, IBT * (T / 64) * C) || al(&iQm, IBH * ((FO + 15) / 16 * 16) * cfg.H) || al(&ibm, IBH * FO) ||
-            al(&iY, F == 2 ? IBH * FO * T : 0) || al(&ishift, (long)IBH * F * cfg.n_rec)) {
-            free_iws();
+        InferWs w;
+        if (!iws && hipMalloc(&iws, infer_ws(nullptr, IBT, IBH, w) * sizeof(float))) {
+            iws = nullptr;
             return sfail(PSTD_ENOMEM, "surrogate inference workspace");
         }
-        iready = true;
         return PSTD_OK;
     }
 };
@@ -1674,33 +1683,35 @@ int infer(sno* s, hipStream_t st, const float* X, int n, float* Y, const float* 
     if (rc) return rc;
     const int T = c.T, TS = T, H = c.H, O = s->O, FO = s->F * O;
     const float* th = s->theta;
+    sno::InferWs w;
+    s->infer_ws(s->iws, std::min<int>(n, sno::IBT), std::min<int>(n, sno::IBH), w);
     for (int b0 = 0; b0 < n; b0 += sno::IBT) {
         const int B = std::min<int>(sno::IBT, n - b0);
         const float* Xb = X + (long)b0 * 9;
         float *V[17], *Vh[16];
-        for (int l = 0; l <= c.L; ++l) V[l] = s->iV[l & 1];
-        for (int l = 0; l < c.L; ++l) Vh[l] = s->iVh;
-        trunk(s, st, Xb, B, TS, nullptr, V, nullptr, Vh, s->iUh, est ? s->ipool : nullptr);
+        for (int l = 0; l <= c.L; ++l) V[l] = w.V[l & 1];
+        for (int l = 0; l < c.L; ++l) Vh[l] = w.Vh;
+        trunk(s, st, Xb, B, TS, nullptr, V, nullptr, Vh, w.Uh, est ? w.pool : nullptr);
         if (est)
-            hipLaunchKernelGGL(k_head_tiles, dim3(B), dim3(64), 0, st, s->ipool, Xb, s->feat, s->dhead, c.C, T,
+            hipLaunchKernelGGL(k_head_tiles, dim3(B), dim3(64), 0, st, w.pool, Xb, s->feat, s->dhead, c.C, T,
                                s->head_margin, est + b0);
         for (int h0 = 0; h0 < B; h0 += sno::IBH) {
             const int Bh = std::min<int>(sno::IBH, B - h0);
             const float* Xh = Xb + (long)h0 * 9;
             float* Yh = Y + (long)(b0 + h0) * O * T;
-            snof::MixP mp{th + s->off_Q2, th + s->off_q2b, Xh, {}, Bh, FO, O, H, s->iQm, s->ibm};
+            snof::MixP mp{th + s->off_Q2, th + s->off_q2b, Xh, {}, Bh, FO, O, H, w.Qm, w.bm};
             for (int j = 0; j < 6; ++j) mp.inv[j] = s->feat.inv[3 + j];
             // (a grid's y dimension ends at 65535: the kernel loops past it)
             hipLaunchKernelGGL(snof::k_qmix_frag, dim3(H / 32, std::min((FO + 15) / 16, 65535)), dim3(128), 0, st,
                                mp);
-            snof::ProjP pp{V[c.L] + (long)h0 * c.C * TS, th + s->off_Q1, th + s->off_q1b, s->iQm, s->ibm,
-                           s->F == 1 ? scale : nullptr, T, TS, H, FO, c.n_rec, 0, 0, 0, s->F == 1 ? Yh : s->iY};
+            snof::ProjP pp{V[c.L] + (long)h0 * c.C * TS, th + s->off_Q1, th + s->off_q1b, w.Qm, w.bm,
+                           s->F == 1 ? scale : nullptr, T, TS, H, FO, c.n_rec, 0, 0, 0, s->F == 1 ? Yh : w.Y};
             proj(s, st, pp, Bh);
             if (s->F == 2) {
                 hipLaunchKernelGGL(k_shifts, dim3((unsigned)std::min<long>(((long)Bh * 2 * c.n_rec + 3) / 4, 8192)),
-                                   dim3(256), 0, st, Xh, s->rays, Bh, s->ishift);
+                                   dim3(256), 0, st, Xh, s->rays, Bh, w.shift);
                 hipLaunchKernelGGL(k_fcomb<2>, dim3((unsigned)std::min<long>((long)Bh * O, 65535)), dim3(256),
-                                   2 * (T + 8) * sizeof(float), st, s->iY, s->ishift, Bh * O, O, c.n_rec, T, scale, Yh);
+                                   2 * (T + 8) * sizeof(float), st, w.Y, w.shift, Bh * O, O, c.n_rec, T, scale, Yh);
             }
         }
     }
