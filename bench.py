@@ -38,17 +38,17 @@ KERNEL_SOURCES = ["paper_1705_04874_amd/csrc/pstd_kernels.hpp", "paper_1705_0487
 # factors a 1 GiB device copy gives) on kernel sources whose digest is recorded here; the
 # summaries are in profiles/.  Reported only while the sources are unchanged.
 MEASURED_TRAFFIC = {
-    "source_digest": "ec476a5be7c561a4",
-    "layered384": {"y_fwd_stress": 1821.6e6, "z_op_V": 2277.2e6, "y_inv_V": 2713.3e6, "vel_update": 3891.0e6,
-                   "y_fwd_vel": 910.8e6, "z_op_S": 1366.5e6, "y_inv_S": 2672.9e6, "stress_update": 5884.9e6},
-    "layered128": {"y_fwd_stress": 102.3e6, "z_op_V": 128.0e6, "y_inv_V": 136.5e6, "vel_update": 250.5e6,
-                   "y_fwd_vel": 51.2e6, "z_op_S": 76.9e6, "y_inv_S": 136.5e6, "stress_update": 377.1e6},
+    "source_digest": "6be53a667ba1db91",
+    "layered384": {"y_fwd_stress": 1821.6e6, "z_op_V": 2277.1e6, "y_inv_V": 2713.1e6, "vel_update": 3891.0e6,
+                   "y_fwd_vel": 910.8e6, "z_op_S": 1366.5e6, "y_inv_S": 2672.3e6, "stress_update": 5884.9e6},
+    "layered128": {"y_fwd_stress": 102.3e6, "z_op_V": 127.8e6, "y_inv_V": 136.5e6, "vel_update": 251.0e6,
+                   "y_fwd_vel": 51.2e6, "z_op_S": 76.9e6, "y_inv_S": 136.5e6, "stress_update": 377.4e6},
 }
 
 # the same for seis_combine's kernel (its own source file): bytes per launch on the
 # bench's combine workload
 COMBINE_SOURCES = ["paper_1705_04874_amd/csrc/combine.hip"]
-COMBINE_TRAFFIC = {"source_digest": "bca329e035f178a8", "bytes": 9486.6e6}
+COMBINE_TRAFFIC = {"source_digest": "8d40f6be9e5f0122", "bytes": 9483.1e6}
 
 
 def kernel_source_digest(files=KERNEL_SOURCES):
@@ -171,7 +171,7 @@ def main():
     ap.add_argument("--workload", default="layered384",
                     choices=["layered384", "layered128", "paper125x75x300", "batched", "combine", "surrogate"],
                     help="batched: 64 shots on the 128^3 model plus 24 uneven models advanced together in one "
-                         "graph per step pair, then seis_combine of 300 events; combine: seis_combine alone "
+                         "call, then seis_combine of 300 events; combine: seis_combine alone "
                          "on the batched configuration's record size; surrogate: training steps and inference "
                          "of the spectral operator surrogate at its full shape")
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -509,7 +509,7 @@ def bench_surrogate(args, binding, inputs, torch):
 def bench_batched(args, binding, inputs, torch):
     """The batched configuration: 64 single-source shots on the 128^3 layered model
     (one context) and 24 uneven models (one context each), advanced together by
-    pstd3d_run_many (one graph per step pair, a stream branch per context); one
+    pstd3d_run_many (each context's step pairs as a graph on its own stream); one
     bench step is a reset of every context plus nt steps of all of them.  Then
     seis_combine sums 300 events of the 64 shots' traces into 12 s records at
     1 ms, timed on its own."""

@@ -22,7 +22,7 @@
 // is.  Longer traces go through k_combine, whose threads own SPT consecutive
 // samples and which stages one source at a time in chunks of STG samples and
 // tests every sample against the chunk (16 x 1024 x 4 traces of 4000 samples
-// into 100 events of 12000: 930 us, and 408 us by whole traces).  Blocks of 512 threads (segments of
+// into a record of 100 events, 12000 samples: 860 us, and 438 us by whole traces).  Blocks of 512 threads (segments of
 // 6144 samples) measured faster than 1024: fewer waves wait at each item's
 // barriers for the busiest one.
 //
